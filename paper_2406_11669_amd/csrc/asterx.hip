@@ -1124,27 +1124,12 @@ DEV T recon_right_face(const T a[5], double eps, double q) {
   return wenoz_face(a[0], a[1], a[2], a[3], a[4], eps, q);
 }
 
-// Transpose of recon_right_face on its active branch: ab[k] = xb d(face value) / d(a[k]).
+// Transpose of recon_right_face on its active branch (MP5, WENO-Z): ab[k] = xb d(face value) / d(a[k]).
 template <int kind>
 DEV void recon_right_face_vjp(const double a[5], double xb, double eps, double q, double ab[5]) {
 #pragma unroll
   for (int k = 0; k < 5; ++k) ab[k] = 0.0;
-  if (kind == ASTERX_RECON_MINMOD) {
-    // a2 + (a2 - a1) / 2 or a2 + (a3 - a2) / 2, whichever difference is smaller; a2 at an extremum
-    const double x = a[2] - a[1], y = a[3] - a[2], h = 0.5 * xb;
-    ab[2] = xb;
-    if (x * y > 0.0) {
-      if (fabs(x) <= fabs(y)) {
-        ab[2] += h;
-        ab[1] -= h;
-      } else {
-        ab[3] += h;
-        ab[2] -= h;
-      }
-    }
-  } else if (kind == ASTERX_RECON_PPM) {
-    ppm_right_vjp(a, xb, ab);
-  } else if (kind == ASTERX_RECON_MP5) {
+  if constexpr (kind == ASTERX_RECON_MP5) {
     Lin5 s[5];
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
@@ -1153,7 +1138,7 @@ DEV void recon_right_face_vjp(const double a[5], double xb, double eps, double q
     }
     const Lin5 r = mp5_face(s[0], s[1], s[2], s[3], s[4]);
 #pragma unroll
-    for (int k = 0; k < 5; ++k) ab[k] = xb * r.c[k];
+    for (int k = 0; k < 5; ++k) ab[k] = xb != 0.0 ? xb * r.c[k] : 0.0;
   } else {
     // WENO-Z: one dual-number pass per stencil value.  Forward mode keeps the tangent of the
     // Z ratio tau / (beta + eps) exact where a smoothness indicator vanishes (eps ~ 1e-40); a
@@ -1163,7 +1148,8 @@ DEV void recon_right_face_vjp(const double a[5], double xb, double eps, double q
       Dual s[5];
 #pragma unroll
       for (int r = 0; r < 5; ++r) s[r] = Dual(a[r], r == k ? 1.0 : 0.0);
-      ab[k] = xb * recon_right_face<kind>(s, eps, q).d;
+      const double d = recon_right_face<kind>(s, eps, q).d;
+      ab[k] = xb != 0.0 ? xb * d : 0.0;  // a side that fell back sends nothing, whatever its slopes
     }
   }
 }
@@ -2366,7 +2352,8 @@ __global__ __launch_bounds__(256) void kb_rk(const PatchDesc* __restrict__ P, co
 // Adjoint workspace: fields of the block's index space.
 enum {
   AW_CONS = 0, AW_PRIM = 5, AW_BC = 10, AW_PBAR = 13, AW_BCBAR = 18, AW_BFBAR = 21, AW_ABAR = 24, AW_PSIBAR = 27,
-  AW_AVBAR = 28, AW_FBAR = 31, AW_FIELDS = 52
+  AW_AVBAR = 28, AW_FBAR = 31, AW_FIELDS = 52,
+  AW_XBAR = AW_ABAR  // seven fields that hold nothing until the faces are done
 };
 // The Gamma cotangent is accumulated into GSLOTS workspace slots (workgroup id modulo GSLOTS):
 // per-wavefront FP64 atomics to one address would serialize in L2.  The slots are summed in a
@@ -2428,7 +2415,8 @@ struct FaceAdjArgs {
   const double* prim;
   const double* A;
   const double* bc;
-  const double* fbar;
+  double* fbar;
+  double* xbar;  // seven fields
   double* pbar;
   double* bcbar;
   double* bfbar;
@@ -2454,8 +2442,7 @@ DEV void face_adj_body(const GD& g, const FaceAdjArgs& fa, unsigned tile) {
     const int st[3] = {1, g.sy, g.sz};
     const int sD = st[D], s1 = st[t1], s2 = st[t2];
     const int o0 = side ? 2 : -3, os = side ? -1 : 1;
-    // forward recomputation of this lane's side (the stencils are loaded again for the transposed
-    // reconstruction at the end rather than held in registers through the reverse sweep)
+    // forward recomputation of this lane's side
     auto field = [&](int v) { return v < 5 ? fa.prim + v * g.N : fa.bc + (v == 5 ? t1 : t2) * g.N; };
     double X[7];
 #pragma unroll
@@ -2582,24 +2569,19 @@ DEV void face_adj_body(const GD& g, const FaceAdjArgs& fa, unsigned tile) {
     // local VJP through (X, Bn, Gamma) -> (U, F, c-, c+): one reverse sweep
     double Xb[7], Bnb, gb;
     side_vjp<D>(G, X, Bn, fa.gam, fa.speeds, cp, cm, Ub, Fb, cmb, cpb, Xb, Bnb, gb);
-    // the normal field is shared by both sides: sum the pair, one store per face.  It and the
-    // stencil loads below come before the scatter: atomics and loads share one counter, so a
-    // load issued after an atomic waits for that atomic to complete.
+    // The cotangents of the two states: the left one's into xbar, the right one's in place of the flux
+    // cotangent (read by both lanes of the pair above).  Unphysical reconstructions used the own cell's values.
+    double* xb = side ? fa.fbar + (size_t)(D * 7) * g.N : fa.xbar;
 #pragma unroll
     for (int v = 0; v < 7; ++v) {
-      double* dst = v < 5 ? fa.pbar + v * g.N : fa.bcbar + (v == 5 ? t1 : t2) * g.N;
       if (fallback) {
+        double* dst = v < 5 ? fa.pbar + v * g.N : fa.bcbar + (v == 5 ? t1 : t2) * g.N;
         atomicAdd(dst + id + (o0 + os * 2) * sD, Xb[v]);
-        continue;
+        Xb[v] = 0.0;
       }
-      double sten[5], ab[5];
-#pragma unroll
-      for (int r = 0; r < 5; ++r) sten[r] = field(v)[id + (o0 + os * r) * sD];
-      recon_right_face_vjp<RECON>(sten, Xb[v], fa.weno_eps, fa.weno_q, ab);
-#pragma unroll
-      for (int q = 0; q < 5; ++q)
-        if (ab[q] != 0.0) atomicAdd(dst + id + (o0 + os * q) * sD, ab[q]);
+      xb[(size_t)v * g.N + id] = Xb[v];
     }
+    // the normal field is shared by both sides: sum the pair, one store per face
     double bn_total = Bnb + shfl1(Bnb);
     if (side == 0) fa.bfbar[(size_t)D * g.N + id] += bn_total;
     gsum = gb;
@@ -2608,6 +2590,114 @@ DEV void face_adj_body(const GD& g, const FaceAdjArgs& fa, unsigned tile) {
 #pragma unroll
   for (int o = 32; o >= 1; o >>= 1) w += __shfl_xor(w, o, 64);
   if (__lane_id() == 0 && w != 0.0) atomicAdd(fa.gbar + (blockIdx.x & (GSLOTS - 1)), w);
+}
+
+// Reconstruction transposed: the cotangents of the states at a direction's faces (left ones in fa.xbar, right
+// ones in fa.fbar) to the cells of their stencils.  Each point gathers what the five cells around it send it,
+// in a fixed order.  As a scatter at the end of the face adjoint, 70 FP64 atomics per face, it set that kernel's
+// time: 64^3, PPM, x/y/z faces 341/222/240 us with the scatter, 72/61/61 us without, and 19/26/26 us here.  The
+// slopes are selected without branches (as branches, whose targets went through scratch: 97/139/137 us).
+// A wavefront takes one variable.  x: 64 consecutive stored points, of which the middle 60 are complete, with
+// the exchange through LDS.  y and z: 64 columns, a march over `rows` points of each (and the two cells
+// before and after them) with the five running sums in registers.
+// Cells in [-1, n] along D have a face of [0, n]; their stencils reach [-3, n + 2], inside the ghosts.
+constexpr int RECON_ADJ_ROWS = 8;
+__host__ __device__ inline unsigned recon_adj_items(const GD& g, int D) {
+  if (D == 0) return (unsigned)(((long long)g.ld0 * (g.n[1] + 1) * (g.n[2] + 1) + 59) / 60 * 7);
+  const long long cols = (long long)(g.n[0] + 1) * (g.n[D == 1 ? 2 : 1] + 1);
+  return (unsigned)((cols + 63) / 64 * ((g.n[D] + 6 + RECON_ADJ_ROWS - 1) / RECON_ADJ_ROWS) * 7);
+}
+
+// Transpose of both face values of the cell of stencil a: ab[k] goes to the point k - 2 from it.
+template <int RECON>
+DEV void recon_cell_vjp(const FaceAdjArgs& fa, const double a[5], double lb, double hb, double ab[5]) {
+  if constexpr (RECON == ASTERX_RECON_MINMOD) {
+    // centre -+ half the smaller difference, or the centre at an extremum
+    const double x = a[2] - a[1], y = a[3] - a[2], h = 0.5 * (hb - lb);
+    const bool up = x * y > 0.0, left = fabs(x) <= fabs(y);
+    const double hl = up && left ? h : 0.0, hr = up && !left ? h : 0.0;
+    ab[0] = ab[4] = 0.0;
+    ab[1] = -hl;
+    ab[2] = hb + lb + hl - hr;
+    ab[3] = hr;
+  } else if constexpr (RECON == ASTERX_RECON_PPM) {
+    ppm_cell_vjp(a, lb, hb, ab);
+  } else {
+    const double b[5] = {a[4], a[3], a[2], a[1], a[0]};
+    double r[5];
+    recon_right_face_vjp<RECON>(a, hb, fa.weno_eps, fa.weno_q, ab);
+    recon_right_face_vjp<RECON>(b, lb, fa.weno_eps, fa.weno_q, r);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) ab[k] += r[4 - k];
+  }
+}
+
+template <int D, int RECON>
+DEV void recon_adj_wave(const GD& g, const FaceAdjArgs& fa, unsigned item, double (*L)[64]) {
+  constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
+  const int sD = D == 0 ? 1 : (D == 1 ? g.sy : g.sz), n = g.n[D];
+  const int v = (int)(item % 7);
+  const unsigned w = item / 7;
+  const double* f = v < 5 ? fa.prim + (size_t)v * g.N : fa.bc + (size_t)(v == 5 ? t1 : t2) * g.N;
+  double* out = v < 5 ? fa.pbar + (size_t)v * g.N : fa.bcbar + (size_t)(v == 5 ? t1 : t2) * g.N;
+  const double* xl = fa.xbar + (size_t)v * g.N;
+  const double* xr = fa.fbar + (size_t)(D * 7 + v) * g.N;
+  if constexpr (D == 0) {
+    const int l = __lane_id();
+    const long long q = (long long)w * 60 + l - 2;
+    const unsigned rows = (unsigned)(g.n[1] + 1) * (g.n[2] + 1);
+    const bool in = q >= 0 && q < (long long)g.ld0 * rows;
+    const unsigned row = in ? (unsigned)q / g.ld0 : 0;
+    const int c = in ? (int)((unsigned)q % g.ld0) - g.ng : -g.ng;
+    const int id = at(g, c, (int)(row % (g.n[1] + 1)) - 1, (int)(row / (g.n[1] + 1)) - 1);
+    double ab[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    if (in && c >= -1 && c <= n) {
+      double a[5];
+#pragma unroll
+      for (int k = 0; k < 5; ++k) a[k] = f[id + k - 2];
+      recon_cell_vjp<RECON>(fa, a, c >= 0 ? xr[id] : 0.0, c < n ? xl[id + 1] : 0.0, ab);
+    }
+#pragma unroll
+    for (int k = 0; k < 5; ++k) L[k][l] = ab[k];
+    wave_lds_sync();
+    // the cell k - 2 below sends its k-th contribution here; rows end in points that get none
+    if (in && l >= 2 && l < 62 && c >= -3 && c <= n + 2) {
+      double t = 0.0;
+#pragma unroll
+      for (int k = 0; k < 5; ++k) t += L[k][l - k + 2];
+      out[id] += t;
+    }
+  } else {
+    const unsigned nx = (unsigned)g.n[0] + 1, cols = nx * (unsigned)(g.n[D == 1 ? 2 : 1] + 1);
+    const unsigned nch = (unsigned)(n + 6 + RECON_ADJ_ROWS - 1) / RECON_ADJ_ROWS;
+    const unsigned col = w / nch * 64 + __lane_id();
+    if (col >= cols) return;
+    const int p0 = (int)(w % nch) * RECON_ADJ_ROWS - 3, p1 = min(p0 + RECON_ADJ_ROWS, n + 3);
+    const int x = (int)(col % nx) - 1, o = (int)(col / nx) - 1;
+    const int base = D == 1 ? at(g, x, 0, o) : at(g, x, o, 0);
+    // points inside [-3, n + 2]
+    auto val = [&](int c) { return c >= -3 && c <= n + 2 ? f[base + c * sD] : 0.0; };
+    double a[5], acc[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 1; k < 5; ++k) a[k] = val(p0 - 5 + k);
+#pragma unroll 4
+    for (int c = p0 - 2; c < p1 + 2; ++c) {
+      const int id = base + c * sD;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) a[k] = a[k + 1];
+      a[4] = val(c + 2);
+      double ab[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+      if (c >= -1 && c <= n)
+        recon_cell_vjp<RECON>(fa, a, c >= 0 ? xr[id] : 0.0, c < n ? xl[id + sD] : 0.0, ab);
+      // acc[k] gathers for point c - 2 + k
+#pragma unroll
+      for (int k = 0; k < 5; ++k) acc[k] += ab[k];
+      if (c - 2 >= p0) out[id - 2 * sD] += acc[0];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) acc[k] = acc[k + 1];
+      acc[4] = 0.0;
+    }
+  }
 }
 
 // Geometric sources transposed, one owned cell per thread, over the cell tiles of the forward
@@ -2999,6 +3089,11 @@ __global__ __launch_bounds__(256) void k_fluxbar(GD g, FluxBarArgs a) { fluxbar_
 template <int D, int R>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_face_adj(GD g, FaceAdjArgs fa) {
   face_adj_body<D, R>(g, fa, my_tile());
+}
+template <int D, int R>
+__global__ __launch_bounds__(64) void k_recon_adj(GD g, FaceAdjArgs fa) {
+  __shared__ double L[D == 0 ? 5 : 1][64];
+  recon_adj_wave<D, R>(g, fa, my_tile(), L);
 }
 __global__ __launch_bounds__(256) void k_cell_adj(GD g, CellAdjArgs ca) {
   __shared__ CellLDS S;
@@ -3914,15 +4009,20 @@ int adj_fillT(const GD& g, double* f, int nf, hipStream_t s) {
   return 0;
 }
 
+template <int D, int R>
+int adj_faces_d(const GD& g, const FaceAdjArgs& fa, hipStream_t s) {
+  int rc;
+  const int e[3] = {g.n[0] + 1, g.n[1] + 1, g.n[2] + 1};
+  if ((rc = timed(KT_ADJ, s, [&] { hipLaunchKernelGGL((k_face_adj<D, R>), dim3(face_tiles(e)), dim3(256), 0, s, g, fa); })))
+    return rc;
+  return timed(KT_ADJ, s, [&] { hipLaunchKernelGGL((k_recon_adj<D, R>), dim3(recon_adj_items(g, D)), dim3(64), 0, s, g, fa); });
+}
+
 template <int R>
 int adj_faces_r(const GD& g, const FaceAdjArgs& fa, hipStream_t s) {
   int rc;
-  unsigned nb = tiles_for(PH_FACE, g);
-  if ((rc = timed(KT_ADJ, s, [&] { hipLaunchKernelGGL((k_face_adj<0, R>), dim3(nb), dim3(256), 0, s, g, fa); })))
-    return rc;
-  if ((rc = timed(KT_ADJ, s, [&] { hipLaunchKernelGGL((k_face_adj<1, R>), dim3(nb), dim3(256), 0, s, g, fa); })))
-    return rc;
-  return timed(KT_ADJ, s, [&] { hipLaunchKernelGGL((k_face_adj<2, R>), dim3(nb), dim3(256), 0, s, g, fa); });
+  if ((rc = adj_faces_d<0, R>(g, fa, s)) || (rc = adj_faces_d<1, R>(g, fa, s))) return rc;
+  return adj_faces_d<2, R>(g, fa, s);
 }
 
 int check_adjoint(const asterx_grid* gr, const asterx_params* p, size_t ws_bytes) {
@@ -4031,14 +4131,19 @@ int asterx_rhs_adjoint(const asterx_grid* gr, const asterx_params* p, const doub
   FluxBarArgs fb{rhs_bar, ws + AW_FBAR * g.N};
   nb = box_blocks<64, 4>(ev);
   if ((rc = timed(KT_ADJ, s, [&] { hipLaunchKernelGGL(k_fluxbar, dim3(nb), dim3(256), 0, s, g, fb); }))) return rc;
-  FaceAdjArgs fa{metric, ws + AW_PRIM * g.N, A, ws + AW_BC * g.N, ws + AW_FBAR * g.N, ws + AW_PBAR * g.N,
-                 ws + AW_BCBAR * g.N, ws + AW_BFBAR * g.N, slots, p->gamma, p->weno_eps, p->weno_q, p->speeds,
+  FaceAdjArgs fa{metric, ws + AW_PRIM * g.N, A, ws + AW_BC * g.N, ws + AW_FBAR * g.N, ws + AW_XBAR * g.N,
+                 ws + AW_PBAR * g.N, ws + AW_BCBAR * g.N, ws + AW_BFBAR * g.N, slots, p->gamma, p->weno_eps, p->weno_q, p->speeds,
                  p->riemann};
   if (p->recon == ASTERX_RECON_MINMOD) rc = adj_faces_r<ASTERX_RECON_MINMOD>(g, fa, s);
   else if (p->recon == ASTERX_RECON_PPM) rc = adj_faces_r<ASTERX_RECON_PPM>(g, fa, s);
   else if (p->recon == ASTERX_RECON_MP5) rc = adj_faces_r<ASTERX_RECON_MP5>(g, fa, s);
   else rc = adj_faces_r<ASTERX_RECON_WENOZ>(g, fa, s);
   if (rc) return rc;
+  const long long nx = 7LL * (long long)g.N;
+  if ((rc = timed(KT_ZERO, s, [&] {
+         hipLaunchKernelGGL(k_zero, dim3(pts_blocks(nx)), dim3(256), 0, s, ws + AW_XBAR * g.N, nx);
+       })))
+    return rc;
   CellAdjArgs ca{metric, curv, ws + AW_PRIM * g.N, ws + AW_BC * g.N, rhs_bar, ws + AW_PBAR * g.N,
                  ws + AW_BCBAR * g.N, slots, p->gamma};
   if ((rc = timed(KT_ADJ, s, [&] {

@@ -602,45 +602,38 @@ DEV void ppm_limit(T ac, T& fl, T& fr) {
   fr = flat ? ac : (over_r ? nr : fr);
 }
 
-// Transposes of the reconstructions' active branches (the adjoint's reverse sweep): each adds
-// xb times the derivative of the face value with respect to each stencil value into ab.
-// MC slope: the centred difference, twice the smaller one-sided difference, or zero at an extremum.
-DEV void mc_slope_vjp(double am, double a0, double ap, double sb, double& gm, double& g0, double& gp) {
+// Derivative of the MC slope (the centred difference, twice the smaller one-sided difference, or zero at an
+// extremum) on its active branch: wm for am, wp for ap, -(wm + wp) for a0.
+DEV void mc_slope_weights(double am, double a0, double ap, double& wm, double& wp) {
   const double dl = a0 - am, dr = ap - a0, dc = 0.5 * (ap - am);
-  if (!(dl * dr > 0.0)) return;
   const double adl = fabs(dl), adr = fabs(dr);
-  if (fabs(dc) <= 2.0 * fmin(adl, adr)) {
-    gp += 0.5 * sb;
-    gm -= 0.5 * sb;
-  } else if (adl <= adr) {
-    g0 += 2.0 * sb;
-    gm -= 2.0 * sb;
-  } else {
-    gp += 2.0 * sb;
-    g0 -= 2.0 * sb;
-  }
+  const bool up = dl * dr > 0.0, mid = fabs(dc) <= 2.0 * fmin(adl, adr), left = adl <= adr;
+  wm = up ? (mid ? -0.5 : (left ? -2.0 : 0.0)) : 0.0;
+  wp = up ? (mid ? 0.5 : (left ? 0.0 : 2.0)) : 0.0;
 }
 
-// PPM value at the right face of the middle cell of a[0..4].
-DEV void ppm_right_vjp(const double a[5], double xb, double ab[5]) {
+// Transpose of the PPM values at both faces of the middle cell of a[0..4] on their active branches: ab[k] =
+// hb d(upper face value) / d(a[k]) + lb d(lower face value) / d(a[k]).  Selections, no branches: lanes differ.
+DEV void ppm_cell_vjp(const double a[5], double lb, double hb, double ab[5]) {
   const double sixth = 1.0 / 6.0;
   const double s1 = mc_slope(a[0], a[1], a[2]), s2 = mc_slope(a[1], a[2], a[3]), s3 = mc_slope(a[2], a[3], a[4]);
   const double fl = 0.5 * (a[1] + a[2]) - (s2 - s1) * sixth;
   const double fr = 0.5 * (a[2] + a[3]) - (s3 - s2) * sixth;
   bool flat, over_l, over_r;
   ppm_cases(a[2], fl, fr, flat, over_l, over_r);
-  double flb = 0.0, frb = 0.0;
-  if (flat) ab[2] += xb;
-  else if (over_r) {
-    ab[2] += 3.0 * xb;
-    flb = -2.0 * xb;
-  } else frb = xb;
-  ab[1] += 0.5 * flb;
-  ab[2] += 0.5 * (flb + frb);
-  ab[3] += 0.5 * frb;
-  mc_slope_vjp(a[0], a[1], a[2], flb * sixth, ab[0], ab[1], ab[2]);
-  mc_slope_vjp(a[1], a[2], a[3], (frb - flb) * sixth, ab[1], ab[2], ab[3]);
-  mc_slope_vjp(a[2], a[3], a[4], -frb * sixth, ab[2], ab[3], ab[4]);
+  const double flb = flat ? 0.0 : ((over_r ? -2.0 * hb : 0.0) + (over_l ? 0.0 : lb));
+  const double frb = flat ? 0.0 : ((over_l ? -2.0 * lb : 0.0) + (over_r ? 0.0 : hb));
+  const double cb = flat ? hb + lb : (over_r ? 3.0 * hb : (over_l ? 3.0 * lb : 0.0));
+  double m1, p1, m2, p2, m3, p3;
+  mc_slope_weights(a[0], a[1], a[2], m1, p1);
+  mc_slope_weights(a[1], a[2], a[3], m2, p2);
+  mc_slope_weights(a[2], a[3], a[4], m3, p3);
+  const double b1 = flb * sixth, b2 = (frb - flb) * sixth, b3 = -frb * sixth;
+  ab[0] = b1 * m1;
+  ab[1] = 0.5 * flb - b1 * (m1 + p1) + b2 * m2;
+  ab[2] = cb + 0.5 * (flb + frb) + b1 * p1 - b2 * (m2 + p2) + b3 * m3;
+  ab[3] = 0.5 * frb + b2 * p2 - b3 * (m3 + p3);
+  ab[4] = b3 * p3;
 }
 
 // WENO-Z (Borges et al. 2008) value at the right face of the middle cell of (m2..p2).
