@@ -127,6 +127,12 @@ int asterx_c2p(const asterx_grid* g, const asterx_params* p, const double* metri
  * LINEAR: linear extrapolation from the two nearest owned indices. */
 int asterx_fill_ghosts(const asterx_grid* g, double* f, int32_t nf, const int32_t* kinds, void* stream);
 
+/* Ghost fill of a state's nine fields (five conserved, A, Psi) in one launch: as asterx_fill_ghosts
+ * of fields 0..4 and 8 with kinds_cell and of 5..7 with kinds_A or, where shift (host double[9]) is
+ * given, asterx_fill_ghosts_shift of them. */
+int asterx_fill_state(const asterx_grid* g, double* u, const int32_t* kinds_cell, const int32_t* kinds_A,
+                      const double* shift, void* stream);
+
 /* Periodic ghost fill of nf <= 3 fields with a constant added per period of wrap:
  * f(s) = f(s mod n) + shift[q*3 + d] * floor(s / n) for field q along axis d.  This is the
  * periodic image of a vector potential A = B_mean x r / 2 + (periodic part) of a field with
@@ -255,6 +261,8 @@ int asterx_batch_prim2con(const asterx_batch* b, const asterx_params* p, const d
 int asterx_batch_c2p(const asterx_batch* b, const asterx_params* p, const double* metric, const double* A,
                      double* cons, double* prim, uint8_t* flags, asterx_c2p_stats* stats, void* stream);
 int asterx_batch_fill_ghosts(const asterx_batch* b, double* f, int32_t nf, const int32_t* kinds, void* stream);
+int asterx_batch_fill_state(const asterx_batch* b, double* u, const int32_t* kinds_cell, const int32_t* kinds_A,
+                            void* stream);
 int asterx_batch_rhs(const asterx_batch* b, const asterx_params* p, const double* metric, const double* curv,
                      const double* prim, const double* A, const double* psi, double dt_max, double* rhs, double* red,
                      void* workspace, size_t ws_bytes, void* stream);

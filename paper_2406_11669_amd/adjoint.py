@@ -67,12 +67,7 @@ class Runner:
     # ---- forward pieces (same calls as the plain driver) ------------------------------------------------
 
     def fill_state(self, U):
-        ax.fill_ghosts(self.L, U[0:5], self.wl.bc_cell)
-        if self.wl.A_shift is not None:
-            ax.fill_ghosts_shift(self.L, U[5:8], self.wl.A_shift)
-        else:
-            ax.fill_ghosts(self.L, U[5:8], self.wl.bc_A)
-        ax.fill_ghosts(self.L, U[8:9], self.wl.bc_cell)
+        ax.fill_state(self.L, U, self.wl.bc_cell, self.wl.bc_A, self.wl.A_shift)
 
     def initial_state(self, p, prim):
         """State (9 fields, ghosts filled) from the initial primitives; resets the c2p warm start to prim."""

@@ -76,10 +76,10 @@ def make_rk_outs(outs):
 _lib = None
 
 EXPORTS = ["asterx_version", "asterx_last_error", "asterx_rhs_workspace_size", "asterx_prim2con", "asterx_c2p",
-           "asterx_fill_ghosts", "asterx_fill_ghosts_shift", "asterx_rhs", "asterx_rk_stage", "asterx_zero", "asterx_timing_enable",
+           "asterx_fill_ghosts", "asterx_fill_ghosts_shift", "asterx_fill_state", "asterx_rhs", "asterx_rk_stage", "asterx_zero", "asterx_timing_enable",
            "asterx_timing_read", "asterx_timing_reset", "asterx_timing_name", "asterx_batch_create",
            "asterx_batch_destroy", "asterx_batch_points", "asterx_batch_offset", "asterx_batch_workspace_size",
-           "asterx_batch_prim2con", "asterx_batch_c2p", "asterx_batch_fill_ghosts", "asterx_batch_rhs",
+           "asterx_batch_prim2con", "asterx_batch_c2p", "asterx_batch_fill_ghosts", "asterx_batch_fill_state", "asterx_batch_rhs",
            "asterx_batch_rk_stage", "asterx_adjoint_workspace_size", "asterx_rhs_adjoint", "asterx_c2p_adjoint",
            "asterx_prim2con_adjoint", "asterx_prim2con_points", "asterx_mlp_features", "asterx_mlp_forward",
            "asterx_mlp_grad_workspace_size", "asterx_mlp_grad", "asterx_mlp_adam", "asterx_c2p_points",
@@ -103,6 +103,7 @@ def lib():
         L.asterx_c2p.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp]
         L.asterx_fill_ghosts.argtypes = [vp, vp, ctypes.c_int32, vp, vp]
         L.asterx_fill_ghosts_shift.argtypes = [vp, vp, ctypes.c_int32, vp, vp]
+        L.asterx_fill_state.argtypes = [vp, vp, vp, vp, vp, vp]
         L.asterx_rhs.argtypes = [vp, vp, vp, vp, vp, vp, vp, ctypes.c_double, vp, vp, vp, ctypes.c_size_t, vp]
         L.asterx_rk_stage.argtypes = [vp, ctypes.c_int32, vp, vp, ctypes.c_double, vp, vp, vp]
         L.asterx_tmunu.argtypes = [vp, vp, vp, vp, vp, vp, vp]
@@ -133,6 +134,7 @@ def lib():
         L.asterx_batch_prim2con.argtypes = [vp, vp, vp, vp, vp, vp, vp]
         L.asterx_batch_c2p.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp]
         L.asterx_batch_fill_ghosts.argtypes = [vp, vp, ctypes.c_int32, vp, vp]
+        L.asterx_batch_fill_state.argtypes = [vp, vp, vp, vp, vp]
         L.asterx_batch_rhs.argtypes = [vp, vp, vp, vp, vp, vp, vp, ctypes.c_double, vp, vp, vp, ctypes.c_size_t,
                                        vp]
         L.asterx_batch_rk_stage.argtypes = [vp, ctypes.c_int32, vp, vp, ctypes.c_double, vp, vp, vp]
@@ -246,8 +248,23 @@ def fill_ghosts_shift(layout, f, shift, stream=None):
     _check(lib().asterx_fill_ghosts_shift(ctypes.byref(make_grid(layout)), _ptr(_f64(f)), nf, sh, _stream(stream)))
 
 
+def _kinds(kinds):
+    return (ctypes.c_int32 * 3)(*[BC[k] if isinstance(k, str) else int(k) for k in kinds])
+
+
+def fill_state(layout, u, kinds_cell, kinds_A, A_shift=None, stream=None):
+    """Ghosts of a nine-field state in one launch: A by kinds_A or, with A_shift, as fill_ghosts_shift fills it."""
+    sh = None
+    if A_shift is not None:
+        sh = (ctypes.c_double * 9)(*np.asarray(A_shift, dtype=np.float64)[:3].ravel().tolist())
+    if u.shape[0] != 9:
+        raise ValueError("fill_state: a state has nine fields")
+    _check(lib().asterx_fill_state(ctypes.byref(make_grid(layout)), _ptr(_f64(u)), _kinds(kinds_cell),
+                                   _kinds(kinds_A), sh, _stream(stream)))
+
+
 def fill_ghosts(layout, f, kinds, stream=None):
-    karr = (ctypes.c_int32 * 3)(*[BC[k] if isinstance(k, str) else int(k) for k in kinds])
+    karr = _kinds(kinds)
     nf = f.shape[0] if f.dim() == 4 else 1
     _check(lib().asterx_fill_ghosts(ctypes.byref(make_grid(layout)), _ptr(_f64(f)), nf, karr, _stream(stream)))
 
@@ -495,15 +512,7 @@ class Block:
         fill_ghosts(self.L, self.state[0:5], wl.bc_cell)
 
     def fill_state(self, U):
-        if self.wl.A_shift is None and tuple(self.wl.bc_A) == tuple(self.wl.bc_cell):
-            fill_ghosts(self.L, U, self.wl.bc_cell)  # all nine fields alike: one launch per axis
-            return
-        fill_ghosts(self.L, U[0:5], self.wl.bc_cell)
-        if self.wl.A_shift is not None:
-            fill_ghosts_shift(self.L, U[5:8], self.wl.A_shift)
-        else:
-            fill_ghosts(self.L, U[5:8], self.wl.bc_A)
-        fill_ghosts(self.L, U[8:9], self.wl.bc_cell)
+        fill_state(self.L, U, self.wl.bc_cell, self.wl.bc_A, self.wl.A_shift)
 
     def at_time(self, t):
         """Switch to the metric of time t when the spacetime is time dependent."""
@@ -671,13 +680,10 @@ class Batch:
         _check(getattr(lib(), name)(self.h, *args))
 
     def fill(self, f, kinds):
-        karr = (ctypes.c_int32 * 3)(*[BC[k] if isinstance(k, str) else int(k) for k in kinds])
-        self._call("asterx_batch_fill_ghosts", _ptr(f), f.shape[0], karr, _stream(None))
+        self._call("asterx_batch_fill_ghosts", _ptr(f), f.shape[0], _kinds(kinds), _stream(None))
 
     def fill_state(self, U):
-        self.fill(U[0:5], self.bc_cell)
-        self.fill(U[5:8], self.bc_A)
-        self.fill(U[8:9], self.bc_cell)
+        self._call("asterx_batch_fill_state", _ptr(U), _kinds(self.bc_cell), _kinds(self.bc_A), _stream(None))
 
     def rk(self, a, us, b_dt, rhs_t, out):
         n = len(a)

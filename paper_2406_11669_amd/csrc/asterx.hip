@@ -928,85 +928,59 @@ DEV void c2p_body(const GD& g, const C2PParams& P, const C2PArgs& a, TileLDS& S,
   }
 }
 
-// Ghost fill along axis d of nf fields.
-struct FillArgs {
-  double* f;
-  int nf;
-  int d;
-  int kind;
-  double shift[3];  // periodic kind: added per period of wrap, for fields 0..2 (else 0)
-};
-
-// Ghost points along axis d: the ghost index set of axis d times the full extents of the
-// other two axes; one thread per point, looping over the nf fields.
-DEV long long fill_points(const GD& g, int d) {
+// Ghost points along axis d: the ghost index set of axis d times the full extents of the other two axes.
+__host__ __device__ inline long long fill_points(const GD& g, int d) {
   long long cnt = 2 * g.ng + 1;
   for (int t = 0; t < 3; ++t)
     if (t != d) cnt *= (g.n[t] + 2 * g.ng + 1);
   return cnt;
 }
 
-DEV void fill_body(const GD& g, const FillArgs& a, unsigned tile) {
-  // ghost values are a pure function of owned values: no contraction, so that linear
-  // extrapolation rounds exactly like its definition (one multiply, then one add)
-#pragma clang fp contract(off)
-  const int d = a.d;
-  int cnt[3] = {g.n[0] + 2 * g.ng + 1, g.n[1] + 2 * g.ng + 1, g.n[2] + 2 * g.ng + 1};
-  cnt[d] = 2 * g.ng + 1;
-  long long tid = (long long)tile * 256 + threadIdx.x;
-  if (tid >= (long long)cnt[0] * cnt[1] * cnt[2]) return;
-  int q0 = (int)(tid % cnt[0]);
-  long long r = tid / cnt[0];
-  int q1 = (int)(r % cnt[1]);
-  int q2 = (int)(r / cnt[1]);
-  int idx[3] = {q0 - g.ng, q1 - g.ng, q2 - g.ng};
-  int n = g.n[d];
-  int q = idx[d] + g.ng;  // 0 .. 2 ng
-  int s = q < g.ng ? q - g.ng : n + (q - g.ng);
-  idx[d] = s;
-  int dst = at(g, idx[0], idx[1], idx[2]);
-  int stride = d == 0 ? 1 : (d == 1 ? g.sy : g.sz);
-  for (int f = 0; f < a.nf; ++f) {
-    double* F = a.f + (size_t)f * g.N;
-    double val;
-    if (a.kind == ASTERX_BC_PERIODIC) {
-      int src = ((s % n) + n) % n;
-      val = F[dst + (src - s) * stride];
-      if (f < 3 && a.shift[f] != 0.0) val = val + (double)((s - src) / n) * a.shift[f];
-    } else if (a.kind == ASTERX_BC_COPY) {
-      int src = s < 0 ? 0 : n - 1;
-      val = F[dst + (src - s) * stride];
-    } else {
-      if (s < 0) {
-        double f0 = F[dst - s * stride], f1 = F[dst + (1 - s) * stride];
-        val = f0 + (double)s * (f1 - f0);
-      } else {
-        double f0 = F[dst + (n - 1 - s) * stride], f1 = F[dst + (n - 2 - s) * stride];
-        val = f0 + (double)(s - n + 1) * (f0 - f1);
-      }
-    }
-    F[dst] = val;
-  }
-}
-
-// One-pass ghost fill when no axis extrapolates (periodic and copy kinds: every ghost point is a
-// remapped owned point): the ghost points of x (all y, z), of y (owned x, all z) and of z (owned x,
-// y) in one launch, each read from the owned point its per-axis maps reach; periodic offsets are
-// added axis by axis in x, y, z order, exactly as the three axis passes add them, so the result is
-// the same bit for bit.
-struct Fill1Args {
+// Ghost fill in one pass: the ghost points of x (all y, z), of y (owned x, all z) and of z (owned x, y), one
+// thread per point.  Defined as axis passes (x, then y, then z), each over the full extents of the others; every
+// ghost value is then a function of owned points: one per axis whose kind copies or wraps, two per axis that
+// extrapolates, combined in x, y, z order as the passes would, so the result is theirs bit for bit (no
+// contraction: linear extrapolation is one multiply, then one add; periodic offsets are added axis by axis).
+// Up to three groups of consecutive fields with kinds of their own, so that a state is one launch: small blocks
+// pay for the launches (a state with an extrapolated potential took five: 16^3, two stages per step, 181 -> 148 us
+// per step), and in batches the ghosts' index arithmetic is done once (64 patches: 190 -> 125 us per stage).
+struct FillArgs {
   double* f;
-  int nf;
-  int kind[3];
-  double shift[3][3];  // [field][axis], fields 0..2
+  int ngroup;
+  int end[3];        // fields [end[q - 1], end[q])
+  int kind[3][3];    // [group][axis]
+  int shifted;       // the group of at most three fields whose periodic wraps add shift, or -1
+  double shift[3][3];  // [field of the group][axis]
 };
 
-DEV long long fill1_points(const GD& g) {
-  const long long G = 2 * g.ng + 1, E1 = g.n[1] + 2 * g.ng + 1, E2 = g.n[2] + 2 * g.ng + 1;
-  return G * E1 * E2 + (long long)g.n[0] * G * E2 + (long long)g.n[0] * g.n[1] * G;
+// The values K fields (st apart) get at a ghost point where some axes extrapolate (bits of lin): o0 the source
+// offsets per axis, o1 the second ones, c their weights.
+template <int K>
+struct FillVals {
+  double v[K];
+};
+template <int K>
+DEV FillVals<K> fill_values(const double* F, size_t st, const int o0[3], const int o1[3], const double c[3], int lin) {
+#pragma clang fp contract(off)
+  auto mix = [](const FillVals<K>& a, const FillVals<K>& b, double w) {
+    FillVals<K> r;
+#pragma unroll
+    for (int k = 0; k < K; ++k) r.v[k] = a.v[k] + w * (b.v[k] - a.v[k]);
+    return r;
+  };
+  auto f = [&](int o) {
+    FillVals<K> r;
+#pragma unroll
+    for (int k = 0; k < K; ++k) r.v[k] = F[k * st + o];
+    return r;
+  };
+  auto fx = [&](int o) { return lin & 1 ? mix(f(o + o0[0]), f(o + o1[0]), c[0]) : f(o + o0[0]); };
+  auto fy = [&](int o) { return lin & 2 ? mix(fx(o + o0[1]), fx(o + o1[1]), c[1]) : fx(o + o0[1]); };
+  return lin & 4 ? mix(fy(o0[2]), fy(o1[2]), c[2]) : fy(o0[2]);
 }
 
-DEV void fill1_body(const GD& g, const Fill1Args& a, unsigned tile) {
+template <bool LIN>
+DEV void fill_body(const GD& g, const FillArgs& a, double* __restrict__ u, unsigned tile) {
 #pragma clang fp contract(off)
   const int ng = g.ng, G = 2 * ng + 1;
   const int E1 = g.n[1] + 2 * ng + 1;
@@ -1033,30 +1007,71 @@ DEV void fill1_body(const GD& g, const Fill1Args& a, unsigned tile) {
   } else {
     return;
   }
-  int src[3], wrap[3];
+  const int dst = at(g, idx[0], idx[1], idx[2]), st[3] = {1, g.sy, g.sz}, org = at(g, 0, 0, 0);
+  int begin = 0;
+#pragma unroll 1
+  for (int q = 0; q < a.ngroup; ++q) {
+    const int end = a.end[q];
+    int o0[3], o1[3], wrap[3], lin = 0;
+    double c[3];
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    const int sd = idx[d], n = g.n[d];
-    if (sd >= 0 && sd < n) {
-      src[d] = sd;
+    for (int d = 0; d < 3; ++d) {
+      const int s = idx[d], n = g.n[d], kind = a.kind[q][d];
+      int src = s, second = s;
       wrap[d] = 0;
-    } else if (a.kind[d] == ASTERX_BC_PERIODIC) {
-      src[d] = ((sd % n) + n) % n;
-      wrap[d] = (sd - src[d]) / n;
-    } else {
-      src[d] = sd < 0 ? 0 : n - 1;
-      wrap[d] = 0;
+      c[d] = 0.0;
+      if (s < 0 || s >= n) {
+        if (kind == ASTERX_BC_PERIODIC) {
+          src = ((s % n) + n) % n;
+          wrap[d] = (s - src) / n;
+        } else {
+          src = s < 0 ? 0 : n - 1;
+          if (LIN && kind == ASTERX_BC_LINEAR) {
+            // f(0) + s (f(1) - f(0)); f(n-1) + (n - 1 - s) (f(n-2) - f(n-1))
+            second = s < 0 ? 1 : n - 2;
+            c[d] = (double)(s < 0 ? s : n - 1 - s);
+            lin |= 1 << d;
+          }
+        }
+      }
+      o0[d] = src * st[d] + (d == 0 ? org : 0);
+      o1[d] = second * st[d] + (d == 0 ? org : 0);
     }
-  }
-  const int dst = at(g, idx[0], idx[1], idx[2]), so = at(g, src[0], src[1], src[2]);
-  for (int f = 0; f < a.nf; ++f) {
-    double* F = a.f + (size_t)f * g.N;
-    double val = F[so];
-    if (f < 3)
+    const int so = o0[0] + o0[1] + o0[2];
+    if (LIN && lin) {
+      int f = begin;
+#pragma unroll 1
+      for (; f + 3 <= end; f += 3) {
+        const FillVals<3> v = fill_values<3>(u + (size_t)f * g.N, g.N, o0, o1, c, lin);
 #pragma unroll
-      for (int d = 0; d < 3; ++d)
-        if (wrap[d] != 0 && a.shift[f][d] != 0.0) val = val + (double)wrap[d] * a.shift[f][d];
-    F[dst] = val;
+        for (int k = 0; k < 3; ++k) u[(size_t)(f + k) * g.N + dst] = v.v[k];
+      }
+#pragma unroll 1
+      for (; f < end; ++f) u[(size_t)f * g.N + dst] = fill_values<1>(u + (size_t)f * g.N, g.N, o0, o1, c, lin).v[0];
+    } else if (q == a.shifted) {
+      for (int f = begin; f < end; ++f) {
+        double* F = u + (size_t)f * g.N;
+        double v = F[so];
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+          if (wrap[d] != 0 && a.shift[f - begin][d] != 0.0) v = v + (double)wrap[d] * a.shift[f - begin][d];
+        F[dst] = v;
+      }
+    } else {
+      // the loads of several fields in flight together: a field's store may not be overtaken by the next loads
+      int f = begin;
+#pragma unroll 1
+      for (; f + 5 <= end; f += 5) {
+        double v[5];
+#pragma unroll
+        for (int k = 0; k < 5; ++k) v[k] = u[(size_t)(f + k) * g.N + so];
+#pragma unroll
+        for (int k = 0; k < 5; ++k) u[(size_t)(f + k) * g.N + dst] = v[k];
+      }
+#pragma unroll 1
+      for (; f < end; ++f) u[(size_t)f * g.N + dst] = u[(size_t)f * g.N + so];
+    }
+    begin = end;
   }
 }
 
@@ -2203,26 +2218,15 @@ __global__ __launch_bounds__(256) void kb_c2p(const PatchDesc* __restrict__ P, c
   }
 }
 
-__global__ __launch_bounds__(256) void k_fill(GD g, FillArgs a) { fill_body(g, a, blockIdx.x); }
-__global__ __launch_bounds__(256) void k_fill1(GD g, Fill1Args a) { fill1_body(g, a, blockIdx.x); }
-__global__ __launch_bounds__(256) void kb_fill1(const PatchDesc* __restrict__ P, const Item* __restrict__ it, int nit,
-                                                Fill1Args a) {
-  for (int w = blockIdx.x; w < nit; w += gridDim.x) {
-    const Item m = it[w];
-    const PatchDesc d = P[m.patch];
-    Fill1Args b = a;
-    b.f = a.f + d.off;
-    fill1_body(d.g, b, (unsigned)m.tile);
-  }
-}
+template <bool LIN>
+__global__ __launch_bounds__(256) void k_fill(GD g, FillArgs a) { fill_body<LIN>(g, a, a.f, blockIdx.x); }
+template <bool LIN>
 __global__ __launch_bounds__(256) void kb_fill(const PatchDesc* __restrict__ P, const Item* __restrict__ it, int nit,
                                                FillArgs a) {
   for (int w = blockIdx.x; w < nit; w += gridDim.x) {
     const Item m = it[w];
     const PatchDesc d = P[m.patch];
-    FillArgs b = a;
-    b.f = a.f + d.off;
-    fill_body(d.g, b, (unsigned)m.tile);
+    fill_body<LIN>(d.g, a, a.f + d.off, (unsigned)m.tile);
   }
 }
 
@@ -3216,7 +3220,7 @@ int timed(int kind, hipStream_t s, F&& launch) {
 // ---------------------------------------------------------------------------------------
 // Launch targets.  A single block launches one workgroup per tile of each phase; a batch
 // of patches launches a persistent grid over that phase's (patch, tile) work list.
-enum { PH_P2C, PH_C2P, PH_FILLX, PH_FILLY, PH_FILLZ, PH_BCENT, PH_FACE, PH_CELL, PH_VERTEX, PH_EDGE, PH_RK, PH_FILL1,
+enum { PH_P2C, PH_C2P, PH_FILL, PH_BCENT, PH_FACE, PH_CELL, PH_VERTEX, PH_EDGE, PH_RK,
        PH_N };
 
 unsigned host_tile_blocks(const GD& g) {
@@ -3229,19 +3233,10 @@ unsigned tiles_for(int phase, const GD& g) {
     case PH_C2P:
     case PH_CELL:
       return host_tile_blocks(g);
-    case PH_FILLX:
-    case PH_FILLY:
-    case PH_FILLZ: {
-      int d = phase - PH_FILLX;
-      long long cnt = 2 * g.ng + 1;
-      for (int t = 0; t < 3; ++t)
-        if (t != d) cnt *= (g.n[t] + 2 * g.ng + 1);
-      return (unsigned)((cnt + 255) / 256);
-    }
     case PH_BCENT:
       for (int a = 0; a < 3; ++a) e[a] = g.n[a] + 2 * g.ng;
       return lin_blocks(e);
-    case PH_FILL1: {
+    case PH_FILL: {
       const long long G = 2 * g.ng + 1, E1 = g.n[1] + 2 * g.ng + 1, E2 = g.n[2] + 2 * g.ng + 1;
       const long long cnt = G * E1 * E2 + (long long)g.n[0] * G * E2 + (long long)g.n[0] * g.n[1] * G;
       return (unsigned)((cnt + 255) / 256);
@@ -3377,23 +3372,47 @@ int make_stdz(const asterx_mlp* mlp, mlpd::Stdz& z, const char* who) {
   return 0;
 }
 
+int run_fill(const GD& g, const asterx_batch* b, const FillArgs& fa, hipStream_t s) {
+  bool lin = false;
+  for (int q = 0; q < fa.ngroup; ++q)
+    for (int a = 0; a < 3; ++a) lin = lin || fa.kind[q][a] == ASTERX_BC_LINEAR;
+  if (lin) return RUN_PHASE(KT_FILL, PH_FILL, k_fill<true>, kb_fill<true>, fa);
+  return RUN_PHASE(KT_FILL, PH_FILL, k_fill<false>, kb_fill<false>, fa);
+}
+
 int do_fill(const GD& g, const asterx_batch* b, double* f, int nf, const int32_t* kinds, hipStream_t s,
             const double* shift = nullptr) {
-  int rc;
-  if (kinds[0] != ASTERX_BC_LINEAR && kinds[1] != ASTERX_BC_LINEAR && kinds[2] != ASTERX_BC_LINEAR) {
-    Fill1Args fa{f, nf, {kinds[0], kinds[1], kinds[2]}, {{0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}, {0.0, 0.0, 0.0}}};
-    if (shift)
-      for (int q = 0; q < 3 && q < nf; ++q)
-        for (int a = 0; a < 3; ++a) fa.shift[q][a] = shift[q * 3 + a];
-    return RUN_PHASE(KT_FILL, PH_FILL1, k_fill1, kb_fill1, fa);
-  }
+  FillArgs fa{};
+  fa.f = f;
+  fa.ngroup = 1;
+  fa.end[0] = nf;
+  for (int a = 0; a < 3; ++a) fa.kind[0][a] = kinds[a];
+  fa.shifted = shift ? 0 : -1;
+  if (shift)
+    for (int q = 0; q < 3 && q < nf; ++q)
+      for (int a = 0; a < 3; ++a) fa.shift[q][a] = shift[q * 3 + a];
+  return run_fill(g, b, fa, s);
+}
+
+// A state's nine fields: the conserved variables and Psi by kinds_cell, the potential by kinds_A or, with shift,
+// periodic with an offset per wrap.
+int do_fill_state(const GD& g, const asterx_batch* b, double* u, const int32_t* kinds_cell, const int32_t* kinds_A,
+                  const double* shift, hipStream_t s) {
+  FillArgs fa{};
+  fa.f = u;
+  fa.ngroup = 3;
+  fa.end[0] = 5;
+  fa.end[1] = 8;
+  fa.end[2] = 9;
   for (int a = 0; a < 3; ++a) {
-    FillArgs fa{f, nf, a, kinds[a], {0.0, 0.0, 0.0}};
-    if (shift)
-      for (int q = 0; q < 3 && q < nf; ++q) fa.shift[q] = shift[q * 3 + a];
-    if ((rc = RUN_PHASE(KT_FILL, PH_FILLX + a, k_fill, kb_fill, fa))) return rc;
+    fa.kind[0][a] = fa.kind[2][a] = kinds_cell[a];
+    fa.kind[1][a] = shift ? ASTERX_BC_PERIODIC : kinds_A[a];
   }
-  return 0;
+  fa.shifted = shift ? 1 : -1;
+  if (shift)
+    for (int q = 0; q < 3; ++q)
+      for (int a = 0; a < 3; ++a) fa.shift[q][a] = shift[q * 3 + a];
+  return run_fill(g, b, fa, s);
 }
 
 int do_bcent(const GD& g, const double* A, double* bc, hipStream_t s) {
@@ -3496,6 +3515,16 @@ int do_rk(const GD& g, const asterx_batch* b, int32_t nterms, const double* a, c
   ra.rhs = rhs;
   ra.out = out;
   return RUN_PHASE(KT_RK, PH_RK, k_rk, kb_rk, ra);
+}
+
+int check_batch_kinds(const asterx_batch* b, const int32_t* kinds) {
+  for (int a = 0; a < 3; ++a) {
+    if (kinds[a] < 0 || kinds[a] > 2) return fail(ASTERX_EARG, "fill_ghosts: unknown boundary kind");
+    for (int q = 0; q < b->np; ++q)
+      if (kinds[a] == ASTERX_BC_LINEAR && b->gds[q].n[a] < 2)
+        return fail(ASTERX_EARG, "fill_ghosts: LINEAR needs n >= 2");
+  }
+  return 0;
 }
 
 int check_kinds(const asterx_grid* gr, const int32_t* kinds) {
@@ -3648,6 +3677,16 @@ int asterx_fill_ghosts(const asterx_grid* gr, double* f, int32_t nf, const int32
   GD g = make_gd(gr);
   const asterx_batch* b = nullptr;
   return do_fill(g, b, f, nf, kinds, (hipStream_t)stream);
+}
+
+int asterx_fill_state(const asterx_grid* gr, double* u, const int32_t* kinds_cell, const int32_t* kinds_A,
+                      const double* shift, void* stream) {
+  int rc;
+  if ((rc = check_grid(gr, 1))) return rc;
+  if (!u || !kinds_cell || (!kinds_A && !shift)) return fail(ASTERX_EARG, "fill_state: bad arguments");
+  if ((rc = check_kinds(gr, kinds_cell)) || (!shift && (rc = check_kinds(gr, kinds_A)))) return rc;
+  const asterx_batch* b = nullptr;
+  return do_fill_state(make_gd(gr), b, u, kinds_cell, kinds_A, shift, (hipStream_t)stream);
 }
 
 int asterx_fill_ghosts_shift(const asterx_grid* gr, double* f, int32_t nf, const double* shift, void* stream) {
@@ -3938,14 +3977,18 @@ int asterx_batch_c2p(const asterx_batch* b, const asterx_params* p, const double
   return do_c2p(g, b, p, metric, A, cons, prim, flags, stats, (hipStream_t)stream);
 }
 
+int asterx_batch_fill_state(const asterx_batch* b, double* u, const int32_t* kinds_cell, const int32_t* kinds_A,
+                            void* stream) {
+  if (!b || !u || !kinds_cell || !kinds_A) return fail(ASTERX_EARG, "batch_fill_state: bad arguments");
+  int rc;
+  if ((rc = check_batch_kinds(b, kinds_cell)) || (rc = check_batch_kinds(b, kinds_A))) return rc;
+  return do_fill_state(b->gds[0], b, u, kinds_cell, kinds_A, nullptr, (hipStream_t)stream);
+}
+
 int asterx_batch_fill_ghosts(const asterx_batch* b, double* f, int32_t nf, const int32_t* kinds, void* stream) {
   if (!b || !f || !kinds || nf < 1) return fail(ASTERX_EARG, "batch_fill_ghosts: bad arguments");
-  for (int a = 0; a < 3; ++a) {
-    if (kinds[a] < 0 || kinds[a] > 2) return fail(ASTERX_EARG, "fill_ghosts: unknown boundary kind");
-    for (int q = 0; q < b->np; ++q)
-      if (kinds[a] == ASTERX_BC_LINEAR && b->gds[q].n[a] < 2)
-        return fail(ASTERX_EARG, "fill_ghosts: LINEAR needs n >= 2");
-  }
+  int rc;
+  if ((rc = check_batch_kinds(b, kinds))) return rc;
   const GD& g = b->gds[0];
   return do_fill(g, b, f, nf, kinds, (hipStream_t)stream);
 }
@@ -4003,7 +4046,7 @@ int adj_fillT(const GD& g, double* f, int nf, hipStream_t s) {
   int rc;
   for (int a = 2; a >= 0; --a) {
     FillTArgs fa{f, nf, a};
-    unsigned nb = tiles_for(PH_FILLX + a, g);
+    unsigned nb = (unsigned)((fill_points(g, a) + 255) / 256);
     if ((rc = timed(KT_ADJ, s, [&] { hipLaunchKernelGGL(k_fillT, dim3(nb), dim3(256), 0, s, g, fa); }))) return rc;
   }
   return 0;
