@@ -385,6 +385,29 @@ int asterx_rhs_rk_src(const asterx_grid* g, const asterx_params* p, const double
                       const double* A, const double* psi, const double* src, double dt_max, int32_t nout,
                       const asterx_rk_out* outs, double* red, void* workspace, size_t ws_bytes, void* stream);
 
+/* ---- One stage with the interpolated spacetime data stored ---------------------------------
+ * The metric at faces and centres, its derivatives and the centre curvature depend on the spacetime
+ * only: a Runge-Kutta step whose stages share a metric interpolates them once.
+ * asterx_geometry: geo (device, ASTERX_GEO_FIELDS fields of the block's index space, out): fields 0-9,
+ * 10-19, 20-29 the ten metric components at the x, y and z faces (Sec. 3.2; owned faces and the
+ * transverse layers the electric field needs, more of them under upwind CT, see p->ct); 30-39 their
+ * centre values, 40-69 their centre derivatives along x, y, z (ten each), 70-75 the centre curvature,
+ * on owned cells.  Reads metric and curv on 2 ghost layers (4 under upwind CT).
+ * asterx_c2p_geo: asterx_c2p_src with the centre data from geo; src: the four densitized sources only.
+ * asterx_rhs_rk_geo: asterx_rhs_rk_src with the face metric from geo (metric: vertex values for the gauge
+ * terms; geo as written for the same metric and p->ct).  The three give the results of asterx_c2p followed
+ * by asterx_rhs_rk up to rounding (the interpolation passes run in another order). */
+#define ASTERX_GEO_FIELDS 76
+int asterx_geometry(const asterx_grid* g, const asterx_params* p, const double* metric, const double* curv, double* geo,
+                    void* stream);
+int asterx_c2p_geo(const asterx_grid* g, const asterx_params* p, const double* geo, const double* A, double* cons,
+                   double* prim, uint8_t* flags, asterx_c2p_stats* stats, const asterx_mlp* mlp, double* src,
+                   void* stream);
+int asterx_rhs_rk_geo(const asterx_grid* g, const asterx_params* p, const double* metric, const double* geo,
+                      const double* prim, const double* A, const double* psi, const double* src, double dt_max,
+                      int32_t nout, const asterx_rk_out* outs, double* red, void* workspace, size_t ws_bytes,
+                      void* stream);
+
 /* Per-kernel timing (diagnostics).  When enabled, every launch of the library is bracketed
  * by two HIP events on its stream; asterx_timing_read waits for the recorded events and
  * returns, for each kernel class k < n, the accumulated milliseconds ms[k] and launch count

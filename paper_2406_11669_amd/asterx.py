@@ -84,7 +84,8 @@ EXPORTS = ["asterx_version", "asterx_last_error", "asterx_rhs_workspace_size", "
            "asterx_prim2con_adjoint", "asterx_prim2con_points", "asterx_mlp_features", "asterx_mlp_forward",
            "asterx_mlp_grad_workspace_size", "asterx_mlp_grad", "asterx_mlp_adam", "asterx_c2p_points",
            "asterx_c2p_learned", "asterx_rhs_rk", "asterx_batch_rhs_rk", "asterx_tmunu", "asterx_prolong",
-           "asterx_restrict", "asterx_rhs_rk_noalloc", "asterx_c2p_src", "asterx_rhs_rk_src"]
+           "asterx_restrict", "asterx_rhs_rk_noalloc", "asterx_c2p_src", "asterx_rhs_rk_src", "asterx_geometry",
+           "asterx_c2p_geo", "asterx_rhs_rk_geo"]
 
 
 def lib():
@@ -113,6 +114,10 @@ def lib():
                                     ctypes.c_size_t, vp]
         L.asterx_c2p_src.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
         L.asterx_rhs_rk_src.argtypes = [vp, vp, vp, vp, vp, vp, vp, ctypes.c_double, ctypes.c_int32, vp, vp, vp,
+                                        ctypes.c_size_t, vp]
+        L.asterx_geometry.argtypes = [vp, vp, vp, vp, vp, vp]
+        L.asterx_c2p_geo.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
+        L.asterx_rhs_rk_geo.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, ctypes.c_double, ctypes.c_int32, vp, vp, vp,
                                         ctypes.c_size_t, vp]
         L.asterx_rhs_rk_noalloc.argtypes = [vp, vp, vp, vp, vp, vp, vp, ctypes.c_double, ctypes.c_int32, vp, vp,
                                             vp]
@@ -335,6 +340,32 @@ def rhs_rk_src(layout, params, metric, prim, A, psi, src, dt_max, outs, red, wor
                                    workspace.numel() * workspace.element_size(), _stream(stream)))
 
 
+GEO_FIELDS = 76  # ASTERX_GEO_FIELDS: face metric (30), centre metric and derivatives (40), centre curvature (6)
+
+
+def geometry(layout, params, metric, curv, geo, stream=None):
+    """asterx_geometry: the spacetime data interpolated to faces and centres, into geo (GEO_FIELDS fields)."""
+    _check(lib().asterx_geometry(ctypes.byref(make_grid(layout)), ctypes.byref(make_params(params)),
+                                 _ptr(_f64(metric)), _ptr(_f64(curv)), _ptr(_f64(geo)), _stream(stream)))
+
+
+def c2p_geo(layout, params, geo, A, cons, prim, src, flags=None, stats=None, stream=None, mlp=None):
+    """asterx_c2p_geo: the recovery and the four densitized sources (src) with the data of geometry()."""
+    _check(lib().asterx_c2p_geo(ctypes.byref(make_grid(layout)), ctypes.byref(make_params(params)),
+                                _ptr(_f64(geo)), _ptr(_f64(A)), _ptr(_f64(cons)), _ptr(_f64(prim)), _ptr(flags),
+                                _ptr(stats), ctypes.byref(mlp) if mlp is not None else None, _ptr(_f64(src)),
+                                _stream(stream)))
+
+
+def rhs_rk_geo(layout, params, metric, geo, prim, A, psi, src, dt_max, outs, red, workspace, stream=None):
+    """asterx_rhs_rk_geo: asterx_rhs_rk with the data of geometry() and the sources of c2p_geo()."""
+    arr = make_rk_outs(outs)
+    _check(lib().asterx_rhs_rk_geo(ctypes.byref(make_grid(layout)), ctypes.byref(make_params(params)),
+                                   _ptr(_f64(metric)), _ptr(_f64(geo)), _ptr(_f64(prim)), _ptr(_f64(A)),
+                                   _ptr(_f64(psi)), _ptr(_f64(src)), float(dt_max), len(outs), arr, _ptr(red),
+                                   _ptr(workspace), workspace.numel() * workspace.element_size(), _stream(stream)))
+
+
 def rhs_rk_noalloc(layout, params, metric, curv, prim, A, psi, dt_max, outs, red, stream=None):
     """asterx_rhs_rk with the library-held workspace (asterx_rhs_rk_noalloc): no device allocation."""
     arr = make_rk_outs(outs)
@@ -474,9 +505,10 @@ class Block:
     RK2 is Heun's method, RK4 the classical scheme (accumulator form).  With fused=True (the
     default) the right-hand side goes straight into the stage outputs (asterx_rhs_rk; RK4
     alternates two stage buffers so that no output is the state being evaluated); fused=False
-    stores it and combines with asterx_rk_stage.  In the fused form the geometric sources are
-    evaluated by the recovery kernel (asterx_c2p_src + asterx_rhs_rk_src) unless src_in_c2p is
-    False (asterx_c2p + asterx_rhs_rk).  All give bitwise equal states."""
+    stores it and combines with asterx_rk_stage.  In the fused form the metric is interpolated to
+    faces and centres once per step (once per stage metric with metric_fn; asterx_geometry) and the
+    geometric sources are evaluated by the recovery kernel (asterx_c2p_geo + asterx_rhs_rk_geo),
+    unless src_in_c2p is False (asterx_c2p + asterx_rhs_rk).  The two agree up to rounding."""
 
     def __init__(self, wl, device="cuda", fused=True, metric_fn=None, src_in_c2p=True):
         self.fused = fused
@@ -502,7 +534,15 @@ class Block:
         self.k = torch.zeros_like(self.state)
         self.tmp2 = torch.zeros_like(self.state) if fused and wl.rk == 4 else None
         self.ws = torch.empty(workspace_size(self.L) // 8, dtype=torch.float64, device=dev)
-        self.src = torch.zeros((SRC_FIELDS,) + self.L.shape3, dtype=torch.float64, device=dev) if self.src_in_c2p else None
+        self.src = self.geo = None
+        if self.src_in_c2p:
+            try:
+                self.geo = torch.empty((GEO_FIELDS,) + self.L.shape3, dtype=torch.float64, device=dev)
+            except torch.OutOfMemoryError:
+                pass  # blocks without room for the stored geometry interpolate it in every stage
+            self.src = torch.zeros((SRC_FIELDS if self.geo is None else 4,) + self.L.shape3, dtype=torch.float64,
+                                   device=dev)
+        self._stepping = self._geo_held = False  # geo holds the current metric's data (inside a step only)
         self.red = torch.zeros(2, dtype=torch.float64, device=dev)
         self.stats = torch.zeros(6, dtype=torch.int64, device=dev)
         self.flags = torch.zeros(self.L.shape3, dtype=torch.uint8, device=dev)
@@ -518,6 +558,7 @@ class Block:
         """Switch to the metric of time t when the spacetime is time dependent."""
         if self.metric_fn is not None:
             self.metric, self.curv = self.metric_fn(t)
+            self._geo_held = False
 
     def recover(self, U):
         """c2p on U (in place for atmosphere cells) and the primitives' ghosts."""
@@ -532,11 +573,21 @@ class Block:
 
     def stage(self, U, outs):
         """c2p on U, then its right-hand side combined into outs = [(a, us, b_dt, out)]."""
-        if self.src_in_c2p:
+        if self.src_in_c2p and self.geo is None:
             c2p_src(self.L, self.params, self.metric, self.curv, U[5:8], U[0:5], self.prim, self.src, self.flags,
                     self.stats, mlp=self.mlp)
             fill_ghosts(self.L, self.prim, self.wl.bc_cell)
-            rhs_rk_src(self.L, self.params, self.metric, self.prim, U[5:8], U[8:9], self.src, self.dt, outs,
+            rhs_rk_src(self.L, self.params, self.metric, self.prim, U[5:8], U[8:9], self.src, self.dt, outs, self.red,
+                       self.ws)
+            return
+        if self.src_in_c2p:
+            if not self._geo_held:
+                geometry(self.L, self.params, self.metric, self.curv, self.geo)
+                self._geo_held = self._stepping
+            c2p_geo(self.L, self.params, self.geo, U[5:8], U[0:5], self.prim, self.src, self.flags, self.stats,
+                    mlp=self.mlp)
+            fill_ghosts(self.L, self.prim, self.wl.bc_cell)
+            rhs_rk_geo(self.L, self.params, self.metric, self.geo, self.prim, U[5:8], U[8:9], self.src, self.dt, outs,
                        self.red, self.ws)
             return
         self.recover(U)
@@ -544,10 +595,15 @@ class Block:
                self.ws)
 
     def step(self):
-        if self.fused:
-            self._step_fused()
-        else:
-            self._step_stored()
+        # the metric is the caller's between steps: what the last one interpolated is not kept
+        self._stepping, self._geo_held = True, False
+        try:
+            if self.fused:
+                self._step_fused()
+            else:
+                self._step_stored()
+        finally:
+            self._stepping = self._geo_held = False
         self.t += self.dt
 
     def _step_fused(self):

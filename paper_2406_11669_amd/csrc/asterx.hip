@@ -3,8 +3,7 @@
 // One block, one GPU.  Per RK stage the caller runs: asterx_c2p -> asterx_fill_ghosts(prim)
 // -> asterx_rhs -> asterx_rk_stage -> asterx_fill_ghosts(state).  asterx_rhs itself is
 // centre field + six launches:
-//   face<D> (D = x, y, z): reconstruction + face metric + prim->cons + fluxes + speeds + HLLE,
-//                          two lanes per face (left and right state), x-pencil coalesced;
+//   face<D> (D = x, y, z): reconstruction + prim->cons + fluxes + speeds + HLLE, one lane per face;
 //   cell:                  flux divergence + geometric sources + div B, LDS-tiled metric;
 //   vertex:                gauge quantities G_A and F_Psi at vertices;
 //   edge:                  FCT electric field, dA/dt and dPsi/dt.
@@ -108,11 +107,10 @@ DEV bool box_at(const int e[3], unsigned tile, unsigned tid, int& a, int& b, int
 // Linear decomposition of a 3-D box into tiles of 256 consecutive points (x fastest): for
 // per-point kernels over extents that are not multiples of a tile row (n + 2, n + 2 ng).
 DEV bool lin_at(const int e[3], unsigned tile, unsigned tid, int& a, int& b, int& c) {
-  const long long q = (long long)tile * 256 + tid;
-  a = (int)(q % e[0]);
-  const long long t = q / e[0];
-  b = (int)(t % e[1]);
-  c = (int)(t / e[1]);
+  const unsigned q = tile * 256 + tid, t = q / (unsigned)e[0];  // below 2^29 points
+  a = (int)(q % (unsigned)e[0]);
+  b = (int)(t % (unsigned)e[1]);
+  c = (int)(t / (unsigned)e[1]);
   return c < e[2];
 }
 inline unsigned lin_blocks(const int e[3]) { return (unsigned)(((long long)e[0] * e[1] * e[2] + 255) / 256); }
@@ -147,6 +145,7 @@ inline unsigned face_tiles(const int e[3]) { return face_plan(e).per * (unsigned
 // tiles apart).  x faces keep the plane order: their stencils run along x inside the tile and
 // their metric is read once per face, and they measured slower in groups.
 constexpr int FACE_ZG = 8;
+
 template <int D>
 constexpr int face_zg() { return D == 0 ? 1 : FACE_ZG; }
 // Face f (0..127) of `tile`: position (a, b, c), whether the tile is a remainder tile (the
@@ -800,11 +799,69 @@ struct C2PArgs {
   double* src;         // SRC instantiation: densitized sources out, [4] (S_x, S_y, S_z, tau)
 };
 
-// LEARNED: a wavefront with cells that have no usable warm start (previous primitives that are
-// not a physical state: the first recovery of a block, reset or prolonged cells) evaluates the
-// learned guess's network on its 64 cells (through its own part of the tile's LDS, free once the
-// metric passes are done) and seeds Noble's iteration of those cells with it; the other cells,
-// and wavefronts without such cells, start from their previous primitives as in the plain form.
+// A wavefront with cells that have no usable warm start (previous primitives that are not a physical
+// state: the first recovery of a block, reset or prolonged cells) evaluates the learned guess's network on
+// its 64 cells (through F and Y, LDS of its own) and seeds Noble's iteration of those cells with it; the
+// other cells, and wavefronts without such cells, start from their previous primitives as in the plain
+// form.  Returns whether zw holds a seed.  Every lane of the wavefront must call it.
+DEV bool learned_seed(const C2PArgs& a, const C2PParams& P, const Geo& G, const double U[5], const double Bt[3],
+                      const double prev[5], bool valid, float (*F)[mlpd::NI], float (*Y)[mlpd::NO], double zw[2]) {
+  using namespace mlpd;
+  const int l = __lane_id(), lr = l & 15, lg = l >> 4;
+  float f[NI];
+  bool usable = false;
+  C2PIn c;
+  bool in = valid && isfinite(U[0]) && isfinite(U[1]) && isfinite(U[2]) && isfinite(U[3]) && isfinite(U[4]) &&
+            U[0] >= G.sqrtg * P.rho_atm;
+  if (in) in = !warm_usable(G, prev, P);
+  // the network runs for whole wavefronts only (matrix instructions), and only where it is needed
+  if (__ballot(in) == 0) return false;
+  if (in) {
+    c2p_input(G, U, Bt, c);
+    features(G, c, P.gam, f, usable);
+  }
+#pragma unroll
+  for (int k = 0; k < NI; ++k) F[l][k] = usable ? (f[k] - a.z.is[k]) * a.z.isc[k] : 0.0f;
+  wave_lds_sync();
+  f4 y[4];
+  mlp_fwd<false>(a.mlp, F, y, nullptr);
+  if (lg == 0)
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+      for (int q = 0; q < NO; ++q) Y[nt * 16 + lr][q] = a.z.os[q] + y[nt][q] / a.z.osc[q];
+  wave_lds_sync();
+  if (!usable) return false;
+  const double W = (double)__expf(Y[l][0]);
+  const double wcap = 1.0 - 1.0 / (P.wmax * P.wmax);
+  zw[0] = c.D * (double)__expf(Y[l][1]);
+  zw[1] = fmin(fmax(1.0 - 1.0 / (W * W), 0.0), wcap);
+  return isfinite(zw[0]) && zw[0] > 0.0;
+}
+
+// Recovery counters of a workgroup: one push, all counters in one instruction (they share a cache line).
+// Pushes to one line serialize in L2, and where most cells fail or are reset (a star in vacuum: 97%) one
+// atomic per wavefront and counter took 4 of the 4.6 ms of a 160^3 launch.  Every thread must call it.
+DEV void c2p_count(uint32_t fl, int iters, unsigned long long* stats) {
+  __shared__ unsigned cnt[4][6];
+  const unsigned it = (unsigned)wave_max_int(iters);
+  const unsigned b[6] = {(unsigned)__popcll(__ballot(fl & 1u)),  (unsigned)__popcll(__ballot(fl & 2u)),
+                         (unsigned)__popcll(__ballot(fl & 4u)),  (unsigned)__popcll(__ballot(fl & 8u)),
+                         (unsigned)__popcll(__ballot(fl & 16u)), it};
+  if (__lane_id() == 0)
+#pragma unroll
+    for (int q = 0; q < 6; ++q) cnt[threadIdx.x >> 6][q] = b[q];
+  __syncthreads();
+  if (threadIdx.x < 6) {
+    const int q = threadIdx.x;
+    const unsigned c0 = cnt[0][q], c1 = cnt[1][q], c2 = cnt[2][q], c3 = cnt[3][q];
+    const unsigned v = q < 5 ? c0 + c1 + c2 + c3 : max(max(c0, c1), max(c2, c3));
+    if (q < 5 && v) atomicAdd(stats + q, (unsigned long long)v);
+    if (q == 5 && v) atomic_max_u64(stats + 5, v);
+  }
+}
+
+// LEARNED: see learned_seed.
 // SRC: the cell's geometric sources (eq. grmhdsrc) follow from the recovered state, with the
 // centre metric of the recovery's own value rounds (the six curvature components join them) and
 // the metric derivative rounds after it; stored densitized, alpha sqrt(gamma) S (rounded on its own).
@@ -815,7 +872,6 @@ DEV void c2p_body(const GD& g, const C2PParams& P, const C2PArgs& a, TileLDS& S,
   double* __restrict__ cons = a.cons;
   double* __restrict__ prim = a.prim;
   uint8_t* __restrict__ flags = a.flags;
-  unsigned long long* __restrict__ stats = a.stats;
   const TileCell t = tile_cell(g, tile);
   const TileIdx x = tile_index(g, t);
   double m[10];
@@ -839,44 +895,12 @@ DEV void c2p_body(const GD& g, const C2PParams& P, const C2PArgs& a, TileLDS& S,
   double zw[2] = {0.0, 0.0};
   bool use_guess = false;
   if constexpr (LEARNED) {
-    using namespace mlpd;
     // F and Y (one part per wavefront) lie in TileLDS's z and y arrays, i.e. over the value rounds'
     // staged vertices and z-pass output, which every thread has finished reading at the barrier
     // before the last x pass; that x pass reads the y-pass output, which lies beyond both
-    float(*F)[64][NI] = reinterpret_cast<float(*)[64][NI]>(S.z);
-    float(*Y)[64][NO] = reinterpret_cast<float(*)[64][NO]>(S.y);
-    const int w = threadIdx.x >> 6, l = __lane_id(), lr = l & 15, lg = l >> 4;
-    float f[NI];
-    bool usable = false;
-    C2PIn c;
-    bool in = t.valid && isfinite(U[0]) && isfinite(U[1]) && isfinite(U[2]) && isfinite(U[3]) && isfinite(U[4]) &&
-              U[0] >= G.sqrtg * P.rho_atm;
-    if (in) in = !warm_usable(G, prev, P);
-    // the network runs for whole wavefronts only (matrix instructions), and only where it is needed
-    if (__ballot(in) != 0) {
-      if (in) {
-        c2p_input(G, U, Bt, c);
-        features(G, c, P.gam, f, usable);
-      }
-#pragma unroll
-      for (int k = 0; k < NI; ++k) F[w][l][k] = usable ? (f[k] - a.z.is[k]) * a.z.isc[k] : 0.0f;
-      wave_lds_sync();
-      f4 y[4];
-      mlp_fwd<false>(a.mlp, F[w], y, nullptr);
-      if (lg == 0)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-          for (int q = 0; q < NO; ++q) Y[w][nt * 16 + lr][q] = a.z.os[q] + y[nt][q] / a.z.osc[q];
-      wave_lds_sync();
-    }
-    if (usable) {
-      const double W = (double)__expf(Y[w][l][0]);
-      const double wcap = 1.0 - 1.0 / (P.wmax * P.wmax);
-      zw[0] = c.D * (double)__expf(Y[w][l][1]);
-      zw[1] = fmin(fmax(1.0 - 1.0 / (W * W), 0.0), wcap);
-      use_guess = isfinite(zw[0]) && zw[0] > 0.0;
-    }
+    const int w = threadIdx.x >> 6;
+    use_guess = learned_seed(a, P, G, U, Bt, prev, t.valid, reinterpret_cast<float(*)[64][mlpd::NI]>(S.z)[w],
+                             reinterpret_cast<float(*)[64][mlpd::NO]>(S.y)[w], zw);
   }
   if (t.valid) {
     fl = c2p_point(G, U, Bt, prev, P, out, iters, use_guess ? zw : nullptr);
@@ -905,27 +929,67 @@ DEV void c2p_body(const GD& g, const C2PParams& P, const C2PArgs& a, TileLDS& S,
 #pragma unroll
       for (int c = 1; c < 5; ++c) a.src[(c - 1) * g.N + id] = __dmul_rn(sw.as, src[c]);
   }
-  if (stats) {
-    // One push per workgroup, all counters in one instruction (they share a cache line): pushes to one
-    // line serialize in L2, and where most cells fail or are reset (a star in vacuum: 97%) one atomic per
-    // wavefront and counter took 4 of the 4.6 ms of a 160^3 launch.
-    __shared__ unsigned cnt[4][6];
-    const unsigned it = (unsigned)wave_max_int(iters);
-    const unsigned b[6] = {(unsigned)__popcll(__ballot(fl & 1u)),  (unsigned)__popcll(__ballot(fl & 2u)),
-                           (unsigned)__popcll(__ballot(fl & 4u)),  (unsigned)__popcll(__ballot(fl & 8u)),
-                           (unsigned)__popcll(__ballot(fl & 16u)), it};
-    if (__lane_id() == 0)
+  if (a.stats) c2p_count(fl, iters, a.stats);
+}
+
+// The recovery and the cell's sources with the interpolated spacetime data given (asterx_geometry): one
+// thread per owned cell, x fastest, no LDS passes and no barriers before the counters.  Per cell it reads
+// 46 interpolated values, 13 of the state and the potential, and writes nine: a streaming kernel.
+struct C2PGeoLDS {
+  float F[4][64][mlpd::NI], Y[4][64][mlpd::NO];
+};
+template <bool LEARNED>
+DEV void c2p_geo_body(const GD& g, const C2PParams& P, const C2PArgs& a, const double* __restrict__ cen, unsigned tile,
+                      C2PGeoLDS* L) {
+  int i, j, k;
+  const bool valid = lin_at(g.n, tile, threadIdx.x, i, j, k);
+  const int id = valid ? at(g, i, j, k) : at(g, 0, 0, 0);
+  uint32_t fl = 0;
+  int iters = 0;
+  Geo G;
+  double m[10], Bt[3], U[5], prev[5], out[5];
 #pragma unroll
-      for (int q = 0; q < 6; ++q) cnt[threadIdx.x >> 6][q] = b[q];
-    __syncthreads();
-    if (threadIdx.x < 6) {
-      const int q = threadIdx.x;
-      const unsigned c0 = cnt[0][q], c1 = cnt[1][q], c2 = cnt[2][q], c3 = cnt[3][q];
-      const unsigned v = q < 5 ? c0 + c1 + c2 + c3 : max(max(c0, c1), max(c2, c3));
-      if (q < 5 && v) atomicAdd(stats + q, (unsigned long long)v);
-      if (q == 5 && v) atomic_max_u64(stats + 5, v);
-    }
+  for (int c = 0; c < 10; ++c) m[c] = ldu(cen + (size_t)c * g.N, id);
+#pragma unroll
+  for (int c = 0; c < 5; ++c) {
+    U[c] = ldu(a.cons + (size_t)c * g.N, id);
+    prev[c] = ldu(a.prim + (size_t)c * g.N, id);
   }
+  centre_B(a.A, g, id, Bt);
+  geo_from(m, G);
+  double zw[2] = {0.0, 0.0};
+  bool use_guess = false;
+  if constexpr (LEARNED) {
+    const int w = threadIdx.x >> 6;
+    use_guess = learned_seed(a, P, G, U, Bt, prev, valid, L->F[w], L->Y[w], zw);
+  }
+  if (valid) {
+    fl = c2p_point(G, U, Bt, prev, P, out, iters, use_guess ? zw : nullptr);
+#pragma unroll
+    for (int c = 0; c < 5; ++c) a.prim[(size_t)c * g.N + id] = out[c];
+    if (fl & 4u) {
+#pragma unroll
+      for (int c = 0; c < 5; ++c) a.cons[(size_t)c * g.N + id] = U[c];
+    }
+    if (a.flags) a.flags[id] = (uint8_t)fl;
+    SrcW sw;
+    src_weights(G, out, Bt, P.gam, sw);
+    double src[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < 10; ++c) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const double v = ldu(cen + (size_t)(10 * (d + 1) + c) * g.N, id);
+        src[d] += sw.w[c] * v;
+        if (c == 0) src[3] += sw.wa[d] * v;
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 6; ++q) src[3] += sw.kc[q] * ldu(cen + (size_t)(40 + q) * g.N, id);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) a.src[(size_t)c * g.N + id] = sw.as * src[c];
+  }
+  if (a.stats) c2p_count(fl, iters, a.stats);
 }
 
 // Ghost points along axis d: the ghost index set of axis d times the full extents of the other two axes.
@@ -1089,37 +1153,147 @@ DEV void bcent_body(const GD& g, const double* __restrict__ A, double* __restric
 }
 
 // ---------------------------------------------------------------------------------------
-// Face fluxes along D.  Face (i,j,k), index along D in [0, n_D], transverse in [-1, n-1]
-// (the extra layer feeds the edge averages of the electric field).
-struct FaceArgs {
+// Spacetime data interpolated once and stored (Sec. 3.2 Lagrange weights): the metric at the faces of
+// each direction, and for the recovery and the sources its centre values and derivatives and the centre
+// curvature.  One lane per x position and R rows (y) marches along z with the last four planes of every pass
+// in registers: per plane the pass along x of the R + 3 vertex rows the rows' y stencils span, the pass along
+// y, then the pass along z.  No LDS and no barriers.  Several rows per lane share their vertex rows.
+// Bound by its 76 streams of stores (128^3, everything: 0.50 ms; stores alone 0.39 to 0.45, loads and arithmetic
+// alone 0.20 to 0.25; one row per lane 0.53, cached instead of nontemporal stores 0.55), once per step, where the
+// four stages' recoveries and faces gathered the same values from the vertices: recovery 0.404 -> 0.271 ms, x, y
+// and z faces 0.214, 0.241, 0.247 -> 0.150, 0.180, 0.198 ms per stage (with the face kernels below).
+// Points: x, y, z in [-lo, n + max(lo - 2, 0)]; a face direction's own index in [0, n], centres owned.
+struct GeomArgs {
   const double* metric;
-  const double* prim;
-  const double* A;
-  const double* bc;
-  double* flux;
-  double* red;
-  double gam, weno_eps, weno_q, gfac;
-  int recon, speeds, riemann;
-  double* apm;  // UCT: a_+, a_- and the normal field per direction
-  // x faces: the x-face metric stored by the recovery with sources over the faces with owned
-  // transverse indices (ten fields indexed like the fluxes), or NULL
-  const double* xfm;
+  const double* curv;
+  // face metric along each direction: components 0..6 from fa, 7..9 from fb (a field apart each)
+  double* fa[3];
+  double* fb[3];
+  double* cen;  // ten values, then d/dx, d/dy, d/dz of the ten, then six curvature values
+  int lo, zl;   // transverse reach of the faces, planes per work item
 };
+enum { GM_X = 1, GM_Y = 2, GM_Z = 4, GM_C = 8 };
+constexpr int GEO_FIELDS = ASTERX_GEO_FIELDS, GEO_CEN = 30;
 
-// Paired-lane variant: lanes 2f and 2f+1 of a wavefront handle the left and the right state
-// of face f.  Each lane reconstructs its own side (the right lane reads its stencil
-// mirrored, so both run the "right face of the middle cell" formula), interpolates half of
-// the face metric, and computes the conserved vector, flux and speeds of its side; the pair
-// exchanges metric halves and side results through lane shuffles and both evaluate HLLE,
-// the left lane storing components 0-3, the right lane 4-6.  Half the live state per lane
-// of a one-lane-per-face kernel, twice the lanes in flight.
-// The swap is a DPP quad permutation (1, 0, 3, 2) of the two 32-bit halves: a VALU move, with no
-// round trip through the LDS crossbar; both lanes of a pair are always active together.
-DEV double shfl1(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_mov_dpp((int)b, 0xB1, 0xF, 0xF, true);
-  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0xB1, 0xF, 0xF, true);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+__host__ __device__ inline void geom_box(const int n[3], int lo, int e[3]) {
+  for (int a = 0; a < 3; ++a) e[a] = n[a] + 2 * lo - 1 + (lo < 2 ? 1 : 0);
+}
+// Planes per item: long marches reload the three planes before their first output less often, short ones
+// fill the chip: with few columns a march of one or two dozen planes is a serial chain of that many loads.
+__host__ __device__ inline int geom_planes(const int e[3]) {
+  const long long waves = ((long long)e[0] * e[1] + 63) / 64 * e[2];
+  return waves >= 16384 ? 16 : (waves >= 2048 ? 8 : 4);
+}
+// Rows per lane: four, or two where the centre data's five rolling quantities leave registers for no more.
+template <int MASK>
+constexpr int geom_rows() { return (MASK & GM_C) ? 2 : 4; }
+inline unsigned geom_items(const GD& g, int lo, int comps, int rows) {
+  int e[3];
+  geom_box(g.n, lo, e);
+  const int zl = geom_planes(e);
+  return (unsigned)(((long long)g.ld0 * ((e[1] + rows - 1) / rows) + 63) / 64 * ((e[2] + zl - 1) / zl) * comps);
+}
+
+// One wavefront's item: component comp of 64 positions (along the stored rows, padding included, so that its
+// loads and stores are whole cache lines) times R rows over zl planes.
+template <int MASK>
+DEV void geom_wave(const GD& g, const GeomArgs& ga, unsigned item) {
+  constexpr int R = geom_rows<MASK>();
+  constexpr bool X = MASK & GM_X, Y = MASK & GM_Y, Z = MASK & GM_Z, C = MASK & GM_C, MARCH = X || Y || C;
+  int e[3];
+  geom_box(g.n, ga.lo, e);
+  const unsigned nrow = (unsigned)(e[1] + R - 1) / R;
+  const unsigned ncol = ((unsigned)g.ld0 * nrow + 63) / 64, nch = (unsigned)(e[2] + ga.zl - 1) / ga.zl;
+  const unsigned col = item % ncol, ch = (item / ncol) % nch, comp = item / (nch * ncol);
+  const int lo = ga.lo;
+  const unsigned q = col * 64 + __lane_id();
+  const int xs = (int)(q % (unsigned)g.ld0) - g.ng, ys = (int)(q / (unsigned)g.ld0) * R - lo;
+  const bool in = xs >= -lo && xs < e[0] - lo && ys < e[1] - lo;
+  const int x = in ? xs : 0, y = in ? ys : 0;
+  const int z0 = (int)ch * ga.zl - lo, z1 = min(z0 + ga.zl, e[2] - lo);
+  const bool curv = C && comp >= 10;
+  const double* f = curv ? ga.curv + (size_t)(comp - 10) * g.N : ga.metric + (size_t)comp * g.N;
+  auto dst = [&](int d) { return comp < 7 ? ga.fa[d] + (size_t)comp * g.N : ga.fb[d] + (size_t)(comp - 7) * g.N; };
+  // rows of the x faces, of the y faces, of the z faces and of the centres
+  const int ty = g.n[1] + lo - 2, tx = g.n[0] + lo - 2;
+  bool fx[R], fy[R], fz[R], own[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    fx[r] = in && !curv && x >= 0 && x <= g.n[0] && y + r <= ty;
+    fy[r] = in && !curv && x <= tx && y + r >= 0 && y + r <= g.n[1];
+    fz[r] = in && !curv && x <= tx && y + r <= ty;
+    own[r] = in && (unsigned)x < (unsigned)g.n[0] && (unsigned)(y + r) < (unsigned)g.n[1];
+  }
+  // the last vertex row a lane's rows need may lie beyond the stored ones where its last rows have no output
+  const int rmax = g.n[1] + g.ng - y;
+  const int base = at(g, x, y, 0);
+  // the last four planes: raw values' y pass, x pass, and the x pass's and its derivative's y passes
+  double wv[R][4], wx[R][4], wy[R][4], wdx[R][4], wdy[R][4];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) wv[r][k] = wx[r][k] = wy[r][k] = wdx[r][k] = wdy[r][k] = 0.0;
+#pragma unroll 4
+  for (int p = MARCH ? z0 - 1 : z0; p < (MARCH ? z1 + 2 : z1); ++p) {
+    const int id = base + p * g.sz;
+    double raw[R + 3], vx[R + 3], dx[R + 3];
+#pragma unroll
+    for (int r = 0; r < R + 3; ++r) {
+      const int o = id + min(r - 1, rmax) * g.sy;
+      const double v0 = ldu(f - 1, o), v1 = ldu(f, o), v2 = ldu(f + 1, o), v3 = ldu(f + 2, o);
+      raw[r] = v1;
+      vx[r] = lag(v0, v1, v2, v3);
+      if constexpr (C) dx[r] = dlag(v0, v1, v2, v3);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        wv[r][k] = wv[r][k + 1];
+        wx[r][k] = wx[r][k + 1];
+        wy[r][k] = wy[r][k + 1];
+        wdx[r][k] = wdx[r][k + 1];
+        wdy[r][k] = wdy[r][k + 1];
+      }
+      if constexpr (X) wv[r][3] = lag(raw[r], raw[r + 1], raw[r + 2], raw[r + 3]);
+      if constexpr (Y) wx[r][3] = vx[r + 1];
+      if constexpr (Z || C) wy[r][3] = lag(vx[r], vx[r + 1], vx[r + 2], vx[r + 3]);
+      if constexpr (C) {
+        wdx[r][3] = lag(dx[r], dx[r + 1], dx[r + 2], dx[r + 3]);
+        wdy[r][3] = dlag(vx[r], vx[r + 1], vx[r + 2], vx[r + 3]);
+      }
+      if constexpr (Z)
+        if (fz[r] && p >= 0 && p <= g.n[2] && p >= z0 && p < z1)
+          __builtin_nontemporal_store(wy[r][3], dst(2) + id + r * g.sy);
+    }
+    if constexpr (MARCH) {
+      const int z = p - 2;
+      if (z < z0) continue;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int o = id - 2 * g.sz + r * g.sy;
+        if (z <= g.n[2] + lo - 2) {
+          if constexpr (X)
+            if (fx[r]) __builtin_nontemporal_store(lag(wv[r][0], wv[r][1], wv[r][2], wv[r][3]), dst(0) + o);
+          if constexpr (Y)
+            if (fy[r]) __builtin_nontemporal_store(lag(wx[r][0], wx[r][1], wx[r][2], wx[r][3]), dst(1) + o);
+        }
+        if constexpr (C)
+          if (own[r] && z >= 0 && z < g.n[2]) {
+            const double val = lag(wy[r][0], wy[r][1], wy[r][2], wy[r][3]);
+            if (curv) {
+              __builtin_nontemporal_store(val, ga.cen + (size_t)(40 + comp - 10) * g.N + o);
+            } else {
+              double* c = ga.cen + (size_t)comp * g.N + o;
+              __builtin_nontemporal_store(val, c);
+              __builtin_nontemporal_store(lag(wdx[r][0], wdx[r][1], wdx[r][2], wdx[r][3]) * g.idx[0], c + 10 * g.N);
+              __builtin_nontemporal_store(lag(wdy[r][0], wdy[r][1], wdy[r][2], wdy[r][3]) * g.idx[1], c + 20 * g.N);
+              __builtin_nontemporal_store(dlag(wy[r][0], wy[r][1], wy[r][2], wy[r][3]) * g.idx[2], c + 30 * g.N);
+            }
+          }
+      }
+    }
+  }
 }
 
 template <int kind, class T>
@@ -1169,415 +1343,328 @@ DEV void recon_right_face_vjp(const double a[5], double xb, double eps, double q
   }
 }
 
-// The x-face metric goes through LDS: a workgroup's 32 x 4 x 1 faces need a vertex block of
-// 32 x 7 x 4 points per component (interpolation in y and z only), loaded once, coalesced
-// along x, into a double buffer (one barrier per component, the next component's loads in
-// flight meanwhile); gathered directly, each wavefront would touch 16 separate rows.  (The
-// same staging serves z faces under WENO-Z, with a 35 x 7 x 1 block.)  The two lanes of a face each
-// interpolate two of the four Lagrange rows and swap them, so both hold all ten components;
-// the arithmetic (rows along t1, then across t2) is the direct 16-point formula's.
-template <int D>
-struct FaceBlk {
-  static constexpr int BX = D == 0 ? 32 : 35, BY = D == 1 ? 4 : 7, BZ = D == 2 ? 1 : 4;
-  static constexpr int N = BX * BY * BZ, NR = (N + 255) / 256;
-};
-constexpr int FACE_LDS = 32 * 7 * 4;
-// y faces stage their reconstruction stencils instead: 7 variables x 9 rows (y) x 32 cells (x)
-constexpr int FACE_RY = 9, FACE_RX = 32, FACE_RV = FACE_RY * FACE_RX, FACE_RN = 7 * FACE_RV;
-// y and z faces of a main tile interpolate their metric in two passes: each lane the 4-point pass
-// across its x column, through a wavefront-private row of 35 columns per component and side, then the
-// 4-point pass along x from that row (a wavefront is one 32-face row of the tile).
-constexpr int FACE_GC = 35;
-struct FaceLDS {
-  union {
-    double m[2][FACE_LDS];
-    double r[FACE_RN];
-    double g[4][5][2][FACE_GC];
-  };
-};
-static_assert(FaceBlk<0>::N <= FACE_LDS && FaceBlk<1>::N <= FACE_LDS && FaceBlk<2>::N <= FACE_LDS, "face LDS");
-
-// UCT: the faces cover transverse indices [-3, n+1] (the upwind edge field reconstructs face
-// values three faces beyond each edge) instead of [-1, n-1], gather directly, and also store the
-// upwind transverse velocities (slots 5, 6 in place of the induction fluxes) and the two speeds.
-template <int D, int RECON, bool UCT = false>
-DEV void face_body(const GD& g, const FaceArgs& fa, unsigned tile, FaceLDS& L) {
-  constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
-  constexpr int LO = UCT ? 3 : 1;
-  using FB = FaceBlk<D>;
-  const int side = threadIdx.x & 1;
-  int e[3] = {g.n[0] + 2 * LO - 1, g.n[1] + 2 * LO - 1, g.n[2] + 2 * LO - 1};
-  e[D] = g.n[D] + 1;
-  int a, b, c;
-  bool rest;
-  int ax0, by0;
-  // both lanes of a pair are valid or invalid together (they share the face); LDS staging
-  // assumes a 32 x 4 tile, so remainder tiles gather directly
-  const bool valid = face_at<face_zg<D>()>(e, tile, threadIdx.x >> 1, a, b, c, rest, ax0, by0);
-  const int cz = c;
-  int ijk[3] = {a - LO, b - LO, c - LO};
-  ijk[D] += LO;
-  const int id = valid ? at(g, ijk[0], ijk[1], ijk[2]) : 0;
-  const int st[3] = {1, g.sy, g.sz};
-  const int sD = st[D];
-  // reconstruction of this lane's side: left lane cells i-3..i+1, right lane i+2..i-2
-  double X[7];
-  auto direct_recon = [&]() {
-    const int o0 = side ? 2 : -3, os = side ? -1 : 1;
-    if constexpr (RECON == ASTERX_RECON_WENOZ && D == 2) {
-      // one variable at a time (the WENO-Z weights of seven variables interleaved would not
-      // fit the register file), the next variable's stencil loading meanwhile (z faces: their
-      // stencil rows are a plane apart; x faces measured faster without the extra registers)
-      auto field = [&](int v) { return v < 5 ? fa.prim + v * g.N : fa.bc + (v == 5 ? t1 : t2) * g.N; };
-      double nx[5];
-#pragma unroll
-      for (int q = 0; q < 5; ++q) nx[q] = ldu(field(0), id + (o0 + os * q) * sD);
-#pragma unroll 1
-      for (int v = 0; v < 7; ++v) {
-        double s5[5];
-#pragma unroll
-        for (int q = 0; q < 5; ++q) s5[q] = nx[q];
-        if (v < 6) {
-          const double* f = field(v + 1);
-#pragma unroll
-          for (int q = 0; q < 5; ++q) nx[q] = ldu(f, id + (o0 + os * q) * sD);
-        }
-        const double xv = recon_right_face<RECON>(s5, fa.weno_eps, fa.weno_q);
-#pragma unroll
-        for (int k = 0; k < 7; ++k) X[k] = v == k ? xv : X[k];
-      }
-    } else if constexpr (RECON == ASTERX_RECON_WENOZ) {
-#pragma unroll 1
-      for (int v = 0; v < 7; ++v) {
-        const double* f = v < 5 ? fa.prim + v * g.N : fa.bc + (v == 5 ? t1 : t2) * g.N;
-        double s5[5];
-#pragma unroll
-        for (int q = 0; q < 5; ++q) s5[q] = ldu(f, id + (o0 + os * q) * sD);
-        const double xv = recon_right_face<RECON>(s5, fa.weno_eps, fa.weno_q);
-#pragma unroll
-        for (int k = 0; k < 7; ++k) X[k] = v == k ? xv : X[k];
-      }
-    } else {
-      // all 35 stencil values are loaded before the first reconstruction
-      double s5[7][5];
-#pragma unroll
-      for (int v = 0; v < 7; ++v) {
-        const double* f = v < 5 ? fa.prim + v * g.N : fa.bc + (v == 5 ? t1 : t2) * g.N;
-#pragma unroll
-        for (int q = 0; q < 5; ++q) s5[v][q] = ldu(f, id + (o0 + os * q) * sD);
-      }
-#pragma unroll
-      for (int v = 0; v < 7; ++v) X[v] = recon_right_face<RECON>(s5[v], fa.weno_eps, fa.weno_q);
-    }
-  };
-  if (D == 1 && RECON == ASTERX_RECON_WENOZ && !UCT && !rest) {
-    // y faces under WENO-Z: the seven stencil fields of the workgroup's 32 x 4 faces (cells y
-    // in [by0 - 3, by0 + 5], x in [ax0 - 1, ax0 + 30]) go through LDS once, coalesced along x
-    // (measured faster for WENO-Z only; PPM and MINMOD keep the direct gather).  The leading
-    // barrier keeps a persistent workgroup's previous item from being overwritten.
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < (FACE_RN + 255) / 256; ++r) {
-      const int q = threadIdx.x + 256 * r;
-      if (q < FACE_RN) {
-        const int v = q / FACE_RV, rem = q % FACE_RV;
-        const int Y = by0 - 3 + rem / FACE_RX, X0 = ax0 - 1 + rem % FACE_RX, Z = cz - 1;
-        const double* f = v < 5 ? fa.prim + v * g.N : fa.bc + (v == 5 ? t1 : t2) * g.N;
-        L.r[q] = (X0 <= g.n[0] + g.ng && Y <= g.n[1] + g.ng) ? f[at(g, X0, Y, Z)] : 0.0;
-      }
-    }
-    __syncthreads();
-    if (valid) {
-      const int o0 = side ? 2 : -3, os = side ? -1 : 1;
-      const int base = (ijk[1] - (by0 - 3)) * FACE_RX + (ijk[0] - (ax0 - 1));
-      auto stencil = [&](int v, double s5[5]) {
-#pragma unroll
-        for (int q = 0; q < 5; ++q) s5[q] = L.r[v * FACE_RV + base + (o0 + os * q) * FACE_RX];
-      };
-#pragma unroll 1
-      for (int v = 0; v < 7; ++v) {
-        double s5[5];
-        stencil(v, s5);
-        const double xv = recon_right_face<RECON>(s5, fa.weno_eps, fa.weno_q);
-#pragma unroll
-        for (int k = 0; k < 7; ++k) X[k] = v == k ? xv : X[k];
-      }
-    }
-  } else if (valid) {
-    direct_recon();
-  }
-  double m[10];
-  // x faces whose transverse indices are all owned (not the y = -1 row block, not the z = -1 plane):
-  // the x-face metric stored by the recovery kernel (each lane loads five components and the pair
-  // swaps them), a workgroup-uniform choice
-  const bool xstored = D == 0 && !UCT && fa.xfm && !rest && by0 >= LO && cz >= LO;
-  // y and z faces: the direct 16-point gather (one transverse direction is x, so a
-  // wavefront's loads are contiguous rows) measured faster than the staged block, except
-  // for z faces under WENO-Z
-  constexpr bool METRIC_LDS = !(D == 1 || (D == 2 && RECON != ASTERX_RECON_WENOZ));
-  // y faces (other than WENO-Z's, whose stencils occupy the LDS) and gathered z faces of main tiles:
-  // the x pass of the face metric is shared through a wavefront-private LDS row
-  // (main tiles are 32 faces wide when the face row is; narrower rows gather directly)
-  constexpr bool METRIC_ROW = !METRIC_LDS && !(D == 1 && RECON == ASTERX_RECON_WENOZ);
-  if (xstored) {
-    if (valid) {
-      double mine[5];
-#pragma unroll
-      for (int q = 0; q < 5; ++q) mine[q] = ldu(fa.xfm + (size_t)(5 * side + q) * g.N, id);
-#pragma unroll
-      for (int q = 0; q < 5; ++q) {
-        double other = shfl1(mine[q]);
-        m[q] = side ? other : mine[q];
-        m[5 + q] = side ? mine[q] : other;
-      }
-    }
-  } else if (METRIC_ROW && !rest && e[0] >= 32) {
-    if (valid) {
-      // the other transverse direction (z for y faces, y for z faces); x is the wavefront's row
-      const int so = D == 1 ? g.sz : g.sy;
-      const int w = threadIdx.x >> 6, f = (threadIdx.x >> 1) & 31;
-      // vertex column x = i - 1 of this lane's face i
-      const int mb = id - so - 1;
-      const double* p0 = fa.metric + (size_t)(5 * side) * g.N + mb;
-      double zc[5], mine[5];
-      // all 20 column loads in one block, so they are in flight together
-#pragma unroll
-      for (int q = 0; q < 5; ++q) {
-        const double* p = p0 + (size_t)q * g.N;
-        zc[q] = lag(p[0], p[so], p[2 * so], p[3 * so]);
-      }
-#pragma unroll
-      for (int q = 0; q < 5; ++q) L.g[w][q][side][f] = zc[q];
-      if (f < 15) {
-        // the 3 columns past the row's end, one (component, column) pair per lane
-        const int q = f / 3, c = f % 3;
-        const double* p = p0 + (size_t)q * g.N + (32 + c - f);
-        L.g[w][q][side][32 + c] = lag(p[0], p[so], p[2 * so], p[3 * so]);
-      }
-      // the row is written and read by this wavefront only (its LDS accesses execute in order): a
-      // wavefront-level barrier keeps the compiler from moving the reads above the writes
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-      for (int q = 0; q < 5; ++q) {
-        const double* row = L.g[w][q][side] + f;
-        mine[q] = lag(row[0], row[1], row[2], row[3]);
-      }
-#pragma unroll
-      for (int q = 0; q < 5; ++q) {
-        double other = shfl1(mine[q]);
-        m[q] = side ? other : mine[q];
-        m[5 + q] = side ? mine[q] : other;
-      }
-    }
-  } else if (!METRIC_LDS || rest) {
-    if (valid) {
-      const int s1 = st[t1], s2 = st[t2];
-      const int mb = id - s1 - s2;
-      double mine[5];
-#pragma unroll
-      for (int q = 0; q < 5; ++q) {
-        const double* p = fa.metric + (size_t)(5 * side + q) * g.N + mb;
-        double rr[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const double* row = p + r * s2;
-          rr[r] = lag(row[0], row[s1], row[2 * s1], row[3 * s1]);
-        }
-        mine[q] = lag(rr[0], rr[1], rr[2], rr[3]);
-      }
-#pragma unroll
-      for (int q = 0; q < 5; ++q) {
-        double other = shfl1(mine[q]);
-        m[q] = side ? other : mine[q];
-        m[5 + q] = side ? mine[q] : other;
-      }
-    }
-  } else if constexpr (D == 0) {
-    // x faces of a main tile: the pass across z is shared by the tile's 4 rows (y).  Each round takes
-    // two components, q for the left lanes and q + 5 for the right ones: the workgroup forms the
-    // z-interpolated values at the tile's 32 x positions and 7 vertex rows y (2 x 7 x 32 items, the
-    // next round's loads in flight meanwhile), stores them in LDS (double-buffered, one barrier per
-    // round), and each lane takes the pass along y over its row's 4 vertex rows.
-    constexpr int NI = 2 * 7 * 32, NIR = (NI + 255) / 256;
-    const int Y0 = by0 - LO - 1, Z0 = cz - LO - 1;
-    int ioff[NIR], isel[NIR];
-#pragma unroll
-    for (int r = 0; r < NIR; ++r) {
-      const int it = threadIdx.x + 256 * r, rem = it % 224;
-      const int X = ax0 + rem % 32, Y = Y0 + rem / 32;
-      const bool in = it < NI && X <= g.n[0] + g.ng && Y <= g.n[1] + g.ng && Z0 + 3 <= g.n[2] + g.ng;
-      ioff[r] = in ? at(g, X, Y, Z0) : -1;
-      isel[r] = it < NI ? it / 224 : 0;  // items past NI (no load) keep a component in range
-    }
-    double pre[NIR][4];
-    auto fetch = [&](int q) {
-#pragma unroll
-      for (int r = 0; r < NIR; ++r) {
-        const double* f = fa.metric + (size_t)(q + 5 * isel[r]) * g.N;
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) pre[r][kk] = ioff[r] >= 0 ? ldu(f, ioff[r] + kk * g.sz) : 0.0;
-      }
-    };
-    fetch(0);
-    const int w = threadIdx.x >> 6, f = (threadIdx.x >> 1) & 31;
-    // a persistent workgroup's previous item read its last round from the buffer the first round
-    // here writes (five rounds, two buffers)
-    __syncthreads();
-#pragma unroll 1
-    for (int q = 0; q < 5; ++q) {
-      double* buf = L.m[q & 1];
-#pragma unroll
-      for (int r = 0; r < NIR; ++r)
-        if (threadIdx.x + 256 * r < NI) buf[threadIdx.x + 256 * r] = lag(pre[r][0], pre[r][1], pre[r][2], pre[r][3]);
-      __syncthreads();
-      if (q < 4) fetch(q + 1);
-      double v = 0.0;
-      if (valid) {
-        const double* p = buf + side * 224 + w * 32 + f;
-        v = lag(p[0], p[32], p[64], p[96]);
-      }
-      const double o = shfl1(v);
-      const double v0 = side ? o : v, v1 = side ? v : o;
-#pragma unroll
-      for (int k = 0; k < 10; ++k) m[k] = k == q ? v0 : (k == q + 5 ? v1 : m[k]);
-    }
+// Both face values of a cell from its five-cell stencil: lo at its lower face (the right state there), hi at
+// its upper one (the left state there).  hi is recon_right_face of the stencil, lo of its mirror image; the
+// two share their slopes (MINMOD, PPM), smoothness indicators and ratios (WENO-Z) and curvatures (MP5).
+template <int kind>
+DEV void recon_cell(const double a[5], double eps, double q, double& lo, double& hi) {
+  if constexpr (kind == ASTERX_RECON_MINMOD) {
+    const double h = 0.5 * mm(a[2] - a[1], a[3] - a[2]);
+    lo = a[2] - h;
+    hi = a[2] + h;
+  } else if constexpr (kind == ASTERX_RECON_PPM) {
+    const double s1 = mc_slope(a[0], a[1], a[2]), s2 = mc_slope(a[1], a[2], a[3]), s3 = mc_slope(a[2], a[3], a[4]);
+    const double sixth = 1.0 / 6.0;
+    lo = 0.5 * (a[1] + a[2]) - (s2 - s1) * sixth;
+    hi = 0.5 * (a[2] + a[3]) - (s3 - s2) * sixth;
+    ppm_limit(a[2], lo, hi);
+  } else if constexpr (kind == ASTERX_RECON_WENOZ) {
+    wenoz_cell(a[0], a[1], a[2], a[3], a[4], eps, q, lo, hi);
   } else {
-    // the block starts one vertex below the first face's transverse position (face index - LO)
-    const int X0 = D == 0 ? ax0 : ax0 - LO - 1, Y0 = D == 1 ? by0 : by0 - LO - 1, Z0 = D == 2 ? cz : cz - LO - 1;
-    int foff[FB::NR];
-    double pre[FB::NR];
+    mp5_cell(a[0], a[1], a[2], a[3], a[4], lo, hi);
+  }
+}
+
+// ---------------------------------------------------------------------------------------
+// Face fluxes along D.  Face (i,j,k), index along D in [0, n_D], transverse in [-1, n-1]
+// (the extra layer feeds the edge averages of the electric field); UCT: transverse in [-3, n+1]
+// (the upwind edge field reconstructs face values three faces beyond each edge), and the upwind
+// transverse velocities (slots 5, 6 in place of the induction fluxes) and the two speeds are stored too.
+struct FaceArgs {
+  const double* metric;
+  const double* prim;
+  const double* A;
+  const double* bc;
+  double* flux;
+  double* red;
+  double gam, weno_eps, weno_q, gfac;
+  int recon, speeds, riemann;
+  double* apm;  // UCT: a_+, a_- and the normal field per direction
+  // face metric per direction, components 0..6 from fma, 7..9 from fmb; NULL: gathered from the vertices
+  const double* fma[3];
+  const double* fmb[3];
+  int rows[3];  // faces per march along y and z
+  bool xown;    // the x faces' stored metric covers the owned rows only
+};
+
+// One lane per face.  A cell's parabola gives the right state at its lower face and the left state at its
+// upper one, so each cell is reconstructed once: x faces with the lanes of a wavefront along x, the left
+// state taken from the lane below (63 faces per wavefront); y and z faces in wavefronts that march along
+// their direction.  Transverse positions are numbered through the whole plane (x faces: the whole block), so
+// rows of any length leave no lanes idle.  The face metric is read as stored.  Against two lanes per face
+// (one per side, each with its own reconstruction, geometry and flux combination): half the
+// reconstructions, inverse metrics and exchanges (128^3, PPM, with the metric read as stored: x, y, z faces 0.214,
+// 0.241, 0.247 -> 0.150, 0.180, 0.198 ms; WENO-Z 0.260, 0.314, 0.308 -> 0.177, 0.218, 0.217).  Bound by FP64 issue:
+// about 1850 vector instructions per face, 0.1 ms of each direction at 128^3.  More wavefronts per SIMD spill, and a
+// workgroup sharing windows through LDS waits at its barriers longer than it saves (both measured slower).
+template <int D>
+DEV void cell_faces_load(const GD& g, const FaceArgs& fa, int v, int id, double s[5]) {
+  constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
+  const int sD = D == 0 ? 1 : (D == 1 ? g.sy : g.sz);
+  const double* f = v < 5 ? fa.prim + (size_t)v * g.N : fa.bc + (size_t)(v == 5 ? t1 : t2) * g.N;
 #pragma unroll
-    for (int r = 0; r < FB::NR; ++r) {
-      const int q = threadIdx.x + 256 * r;
-      const int X = X0 + q % FB::BX, Y = Y0 + (q / FB::BX) % FB::BY, Z = Z0 + q / (FB::BX * FB::BY);
-      const bool in = q < FB::N && X <= g.n[0] + g.ng && Y <= g.n[1] + g.ng && Z <= g.n[2] + g.ng;
-      foff[r] = in ? at(g, X, Y, Z) : -1;
-      pre[r] = in ? ldu(fa.metric, foff[r]) : 0.0;
-    }
-    const int lst[3] = {1, FB::BX, FB::BX * FB::BY};
-    const int ls1 = lst[t1], ls2 = lst[t2];
-    const int lbase = valid ? (a - ax0) + FB::BX * (b - by0) + 2 * side * ls2 : 0;
+  for (int q = 0; q < 5; ++q) s[q] = ldu(f, id + (q - 2) * sD);
+}
+
+// The seven reconstructed variables of cell id at its two D faces: at the lower face into registers, at the
+// upper one into this lane's column of hi (LDS; the left state of the face above).
+typedef double FaceVals[7][64];
+template <int D, int RECON>
+DEV void cell_faces(const GD& g, const FaceArgs& fa, int id, double lo[7], FaceVals& Lhi, FaceVals& Llo) {
+  const int l = __lane_id();
+  if constexpr (RECON != ASTERX_RECON_MINMOD) {
+    // one variable at a time (those of seven interleaved would not fit the registers), the next two variables'
+    // stencils loading meanwhile
+    double n1[5], n2[5];
+    cell_faces_load<D>(g, fa, 0, id, n1);
+    cell_faces_load<D>(g, fa, 1, id, n2);
 #pragma unroll 1
-    for (int q = 0; q < 10; ++q) {
-      double* buf = L.m[q & 1];
+    for (int v = 0; v < 7; ++v) {
+      double s[5], x, y;
 #pragma unroll
-      for (int r = 0; r < FB::NR; ++r)
-        if (threadIdx.x + 256 * r < FB::N) buf[threadIdx.x + 256 * r] = pre[r];
-      __syncthreads();
-      if (q < 9)
-#pragma unroll
-        for (int r = 0; r < FB::NR; ++r) pre[r] = foff[r] >= 0 ? ldu(fa.metric + (size_t)(q + 1) * g.N, foff[r]) : 0.0;
-      double ra = 0.0, rb = 0.0;
-      if (valid) {
-        const double* p = buf + lbase;
-        ra = lag(p[0], p[ls1], p[2 * ls1], p[3 * ls1]);
-        p += ls2;
-        rb = lag(p[0], p[ls1], p[2 * ls1], p[3 * ls1]);
+      for (int q = 0; q < 5; ++q) {
+        s[q] = n1[q];
+        n1[q] = n2[q];
       }
-      const double oa = shfl1(ra), ob = shfl1(rb);
-      const double v = side ? lag(oa, ob, ra, rb) : lag(ra, rb, oa, ob);
+      if (v < 5) cell_faces_load<D>(g, fa, v + 2, id, n2);
+      recon_cell<RECON>(s, fa.weno_eps, fa.weno_q, x, y);
+      Llo[v][l] = x;
+      Lhi[v][l] = y;
+    }
 #pragma unroll
-      for (int k = 0; k < 10; ++k) m[k] = q == k ? v : m[k];
+    for (int v = 0; v < 7; ++v) lo[v] = Llo[v][l];
+  } else {
+    // all 35 stencil values are loaded before the first reconstruction
+    double s[7][5];
+#pragma unroll
+    for (int v = 0; v < 7; ++v) cell_faces_load<D>(g, fa, v, id, s[v]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int v = 0; v < 7; ++v) {
+      double y;
+      recon_cell<RECON>(s[v], fa.weno_eps, fa.weno_q, lo[v], y);
+      Lhi[v][l] = y;
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
-  double smax = 0.0;
-  if (valid) {
-    Geo G;
-    geo_from(m, G);
-    const double* Ax = fa.A;
-    const double* Ay = fa.A + g.N;
-    const double* Az = fa.A + 2 * g.N;
-    double Bn = D == 0 ? faceBx(Ay, Az, id, g.sy, g.sz, g)
-                       : (D == 1 ? faceBy(Ax, Az, id, g.sy, g.sz, g) : faceBz(Ax, Ay, id, g.sy, g.sz, g));
-    // an unphysical reconstructed state falls back to the values of this side's own cell (i-1 for
-    // the left lane, i for the right one), read again (rare) rather than kept in registers
-    {
-      double vl[3], v[3] = {X[2], X[3], X[4]};
-      lower(G.g, v, vl);
-      double v2 = v[0] * vl[0] + v[1] * vl[1] + v[2] * vl[2];
-      if (!(X[0] > 0.0) || !(X[1] > 0.0) || !(v2 < 1.0)) {
-        const int own = side ? id : id - sD;
+  wave_lds_sync();
+}
+
+// State, fluxes and speeds of one side; an unphysical reconstructed state falls back to the values of the
+// side's own cell, read again (rare) rather than kept in registers.
+template <int D>
+DEV void face_side(const GD& g, const FaceArgs& fa, const Geo& G, double Bn, int own, double X[7], double U[7],
+                   double F[7], double& cm, double& cp) {
+  constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
+  double Bt[3];
+  Bt[D] = Bn;
+  Bt[t1] = X[5];
+  Bt[t2] = X[6];
+  State S;
+  state_make(G, X, Bt, fa.gam, S, fa.gfac);
+  if (!(X[0] > 0.0) || !(X[1] > 0.0) || !(S.iW2 > 0.0)) {
 #pragma unroll
-        for (int q = 0; q < 7; ++q) X[q] = ldu(q < 5 ? fa.prim + q * g.N : fa.bc + (q == 5 ? t1 : t2) * g.N, own);
-      }
-    }
-    double Bt[3];
-    Bt[D] = Bn;
+    for (int q = 0; q < 7; ++q) X[q] = ldu(q < 5 ? fa.prim + (size_t)q * g.N : fa.bc + (size_t)(q == 5 ? t1 : t2) * g.N, own);
     Bt[t1] = X[5];
     Bt[t2] = X[6];
-    State S;
     state_make(G, X, Bt, fa.gam, S, fa.gfac);
-    double U[7], F[7], cm, cp;
-    flux_of<D>(G, S, U, F);
-    speeds_of<D>(G, S, fa.gam, fa.speeds, cm, cp);
-    // exchange with the partner lane and combine (HLLE, eq. HLLEfluxes)
-    double Uo[7], Fo[7];
+  }
+  flux_of<D>(G, S, U, F);
+  speeds_of<D>(G, S, fa.gam, fa.speeds, cm, cp);
+}
+
+// What a face reads besides its cells' values: its metric and the normal field from the potential around it.
+// x faces load it before the reconstruction, so that it arrives meanwhile (152 -> 148 us at 128^3; y and z
+// faces, whose marches hold more registers, measured slower so).
+struct FaceIn {
+  double m[10], Bn;
+};
+template <int D>
+DEV void face_load(const GD& g, const FaceArgs& fa, int id, FaceIn& f, bool stored = true) {
+  constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
+  if (fa.fma[D] && stored) {
 #pragma unroll
-    for (int q = 0; q < 7; ++q) {
-      Uo[q] = shfl1(U[q]);
-      Fo[q] = shfl1(F[q]);
-    }
-    double cmo = shfl1(cm), cpo = shfl1(cp);
-    double cmax = fmax(0.0, fmax(cp, cpo));
-    double cmin = -fmin(0.0, fmin(cm, cmo));
-    double den = cmax + cmin;
-    // HLLE: (cmin F_R + cmax F_L - cmax cmin (U_R - U_L)) / (cmax + cmin); LxF (eq. LxFfluxes):
-    // (F_R + F_L - c_wave (U_R - U_L)) / 2, c_wave = max(cmax, cmin).  Written from this lane's
-    // point of view (own side, other side) so no per-component side selects.
-    double w_own, w_oth, w_u;
-    if (fa.riemann == ASTERX_RIEMANN_LXF) {
-      const double hw = 0.5 * fmax(cmax, cmin);
-      w_own = w_oth = 0.5;
-      w_u = side ? -hw : hw;
-    } else {
-      double id_ = den > 0.0 ? recip(den) : 0.0;
-      double cc = cmax * cmin;
-      w_own = den > 0.0 ? (side ? cmin : cmax) * id_ : 0.5;
-      w_oth = den > 0.0 ? (side ? cmax : cmin) * id_ : 0.5;
-      w_u = den > 0.0 ? (side ? -cc : cc) * id_ : 0.0;
-    }
-    double out[7];
+    for (int q = 0; q < 10; ++q) f.m[q] = ldu(q < 7 ? fa.fma[D] + (size_t)q * g.N : fa.fmb[D] + (size_t)(q - 7) * g.N, id);
+  } else {
+    const int st[3] = {1, g.sy, g.sz};
+#pragma unroll 1
+    for (int q = 0; q < 10; ++q) {
+      const double* p = fa.metric + (size_t)q * g.N + (id - st[t1] - st[t2]);
+      double r[4];
 #pragma unroll
-    for (int q = 0; q < 7; ++q) out[q] = w_own * F[q] + w_oth * Fo[q] + w_u * (U[q] - Uo[q]);
-    if constexpr (UCT) {
-      // upwind transverse velocities (eq. uct1) with a_+ = cmax, a_- = cmin (eq. uct2)
-      double vbar[2];
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const int t = k ? t2 : t1;
-        const double vown = G.alp * X[2 + t] - G.beta[t], voth = shfl1(vown);
-        const double vl = side ? voth : vown, vr = side ? vown : voth;
-        vbar[k] = den > 0.0 ? (cmax * vl + cmin * vr) / den : 0.5 * (vl + vr);
+      for (int k = 0; k < 4; ++k) {
+        const double* row = p + k * st[t2];
+        r[k] = lag(row[0], row[st[t1]], row[2 * st[t1]], row[3 * st[t1]]);
       }
-      if (side == 0) {
+      const double v = lag(r[0], r[1], r[2], r[3]);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) fa.flux[(size_t)(D * 7 + q) * g.N + id] = out[q];
-        fa.apm[(size_t)(D * 3) * g.N + id] = cmax;
-        fa.apm[(size_t)(D * 3 + 1) * g.N + id] = cmin;
-        fa.apm[(size_t)(D * 3 + 2) * g.N + id] = Bn;
-      } else {
-        fa.flux[(size_t)(D * 7 + 4) * g.N + id] = out[4];
-        fa.flux[(size_t)(D * 7 + 5) * g.N + id] = vbar[0];
-        fa.flux[(size_t)(D * 7 + 6) * g.N + id] = vbar[1];
-      }
-      if ((unsigned)ijk[t1] < (unsigned)g.n[t1] && (unsigned)ijk[t2] < (unsigned)g.n[t2]) smax = fmax(cmax, cmin);
-    } else {
-      if (side == 0) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) fa.flux[(size_t)(D * 7 + q) * g.N + id] = out[q];
-      } else {
-#pragma unroll
-        for (int q = 4; q < 7; ++q) fa.flux[(size_t)(D * 7 + q) * g.N + id] = out[q];
-      }
-      if (ijk[t1] >= 0 && ijk[t2] >= 0) smax = fmax(cmax, cmin);
+      for (int k = 0; k < 10; ++k) f.m[k] = k == q ? v : f.m[k];
     }
   }
-  if (fa.red) {
-    double w = wave_max(smax);
-    if (__lane_id() == 0) atomic_max_pos(fa.red, w);
+  const double* Ax = fa.A;
+  const double* Ay = fa.A + g.N;
+  const double* Az = fa.A + 2 * g.N;
+  f.Bn = D == 0 ? faceBx(Ay, Az, id, g.sy, g.sz, g)
+                : (D == 1 ? faceBy(Ax, Az, id, g.sy, g.sz, g) : faceBz(Ax, Ay, id, g.sy, g.sz, g));
+}
+
+// The face between the cells of states XL (below) and XR (above), stored at point id; returns the larger speed.
+template <int D, bool UCT>
+DEV double face_solve(const GD& g, const FaceArgs& fa, int id, const FaceIn& in, double XL[7], double XR[7]) {
+  constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
+  const int st[3] = {1, g.sy, g.sz};
+  const double Bn = in.Bn;
+  Geo G;
+  geo_from(in.m, G);
+  double UL[7], FL[7], UR[7], FR[7], cmL, cpL, cmR, cpR;
+  face_side<D>(g, fa, G, Bn, id - st[D], XL, UL, FL, cmL, cpL);
+  __builtin_amdgcn_sched_barrier(0);
+  face_side<D>(g, fa, G, Bn, id, XR, UR, FR, cmR, cpR);
+  const double cmax = fmax(0.0, fmax(cpL, cpR)), cmin = -fmin(0.0, fmin(cmL, cmR));
+  const double den = cmax + cmin;
+  // HLLE (eq. HLLEfluxes): (cmin F_R + cmax F_L - cmax cmin (U_R - U_L)) / (cmax + cmin); LxF (eq. LxFfluxes):
+  // (F_R + F_L - c_wave (U_R - U_L)) / 2, c_wave = max(cmax, cmin)
+  double wl = 0.5, wr = 0.5, wu = 0.0;
+  if (fa.riemann == ASTERX_RIEMANN_LXF) {
+    wu = 0.5 * fmax(cmax, cmin);
+  } else if (den > 0.0) {
+    const double r = recip(den);
+    wl = cmax * r;
+    wr = cmin * r;
+    wu = cmax * cmin * r;
   }
+  double* out = fa.flux + (size_t)(D * 7) * g.N;
+#pragma unroll
+  for (int q = 0; q < (UCT ? 5 : 7); ++q) out[(size_t)q * g.N + id] = wl * FL[q] + wr * FR[q] + wu * (UL[q] - UR[q]);
+  if constexpr (UCT) {
+    // upwind transverse velocities (eq. uct1) with a_+ = cmax, a_- = cmin (eq. uct2)
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int t = k ? t2 : t1;
+      const double vl = G.alp * XL[2 + t] - G.beta[t], vr = G.alp * XR[2 + t] - G.beta[t];
+      out[(size_t)(5 + k) * g.N + id] = den > 0.0 ? (cmax * vl + cmin * vr) / den : 0.5 * (vl + vr);
+    }
+    fa.apm[(size_t)(D * 3) * g.N + id] = cmax;
+    fa.apm[(size_t)(D * 3 + 1) * g.N + id] = cmin;
+    fa.apm[(size_t)(D * 3 + 2) * g.N + id] = Bn;
+  }
+  return fmax(cmax, cmin);
+}
+
+// Wavefront items.  x faces: 63 consecutive faces of the sequence of cells -1..n0 of every row.  y and z
+// faces: 64 transverse columns times a march of `rows` faces, the marches of a column group one after another
+// (the rows that two of them read are then in one XCD's L2).
+__host__ __device__ inline unsigned face_items(const int n[3], int D, int lo, int rows) {
+  int e[3];
+  for (int a = 0; a < 3; ++a) e[a] = n[a] + 2 * lo - 1;
+  if (D == 0) return (unsigned)(((long long)(n[0] + 2) * e[1] * e[2] - 1 + 62) / 63);
+  const long long cols = (long long)e[0] * e[D == 1 ? 2 : 1];
+  return (unsigned)((cols + 63) / 64 * ((n[D] + rows) / rows));
+}
+// Faces per march.  A march of r faces costs r + 1 reconstructions and r solutions (which cost about the same),
+// and its five-row windows have to stay in L2 with those of all marches in flight: at 128^3 with PPM the y + z
+// faces took 0.417 ms in marches of 1, 0.367 of 2, 0.380 of 3, 0.403 of 4, 0.456 of 16, with WENO-Z 0.446 of 2,
+// 0.420 of 3, 0.445 of 4: at most two, WENO-Z three.  Blocks whose marches fill the chip's wavefront slots only a
+// few times take the length whose rounds cost least (48^3, PPM: y faces 20 us in marches of 1, 24 of 2; 96^3: 95
+// and 87 us).
+template <int R>
+constexpr int face_march() { return R == ASTERX_RECON_WENOZ ? 3 : 2; }
+constexpr int FACE_BATCH_ROWS = 2;
+constexpr unsigned FACE_SLOTS = 256 * 4 * 3;  // 256 CUs of four SIMDs, three wavefronts each
+inline int face_rows(const int n[3], int D, int lo, int march) {
+  int best = 1;
+  unsigned least = ~0u;
+  for (int r = 1; r <= march; ++r) {
+    const unsigned cost = (face_items(n, D, lo, r) + FACE_SLOTS - 1) / FACE_SLOTS * (unsigned)(2 * r + 1);
+    if (cost <= least) {
+      least = cost;
+      best = r;
+    }
+  }
+  return best;
+}
+
+// Faces with owned transverse indices report their speed.
+template <int D>
+DEV bool face_owned(const GD& g, const int c[3]) {
+  constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
+  return (unsigned)c[t1] < (unsigned)g.n[t1] && (unsigned)c[t2] < (unsigned)g.n[t2];
+}
+DEV void face_report(const FaceArgs& fa, double smax) {
+  if (!fa.red) return;
+  const double w = wave_max(smax);
+  if (__lane_id() == 0) atomic_max_pos(fa.red, w);
+}
+
+struct FaceLDS {
+  FaceVals hi, lo;
+};
+template <int RECON, bool UCT>
+DEV void face_wave_x(const GD& g, const FaceArgs& fa, unsigned item, FaceLDS& L) {
+  constexpr int lo = UCT ? 3 : 1;
+  const unsigned e1 = g.n[1] + 2 * lo - 1, e2 = g.n[2] + 2 * lo - 1;
+  const unsigned rl = (unsigned)g.n[0] + 2, total = rl * e1 * e2;
+  const unsigned q = min(item * 63 + __lane_id(), total - 1);
+  const unsigned row = q / rl;
+  const int c[3] = {(int)(q % rl) - 1, (int)(row % e1) - lo, (int)(row / e1) - lo};
+  const int id = at(g, c[0], c[1], c[2]);
+  double XL[7], XR[7], smax = 0.0;
+  FaceIn fin;
+  face_load<0>(g, fa, id, fin, !fa.xown || (c[1] >= 0 && c[2] >= 0));
+  cell_faces<0, RECON>(g, fa, id, XR, L.hi, L.lo);
+  wave_lds_sync();
+  if (__lane_id() > 0 && item * 63 + __lane_id() < total && c[0] >= 0) {
+#pragma unroll
+    for (int v = 0; v < 7; ++v) XL[v] = L.hi[v][__lane_id() - 1];
+    const double s = face_solve<0, UCT>(g, fa, id, fin, XL, XR);
+    if (face_owned<0>(g, c)) smax = s;
+  }
+  face_report(fa, smax);
+}
+
+template <int D, int RECON, bool UCT>
+DEV void face_wave_yz(const GD& g, const FaceArgs& fa, unsigned item, FaceLDS& L) {
+  constexpr int lo = UCT ? 3 : 1, E = D == 1 ? 2 : 1;
+  const int rows = fa.rows[D], l = __lane_id();
+  const unsigned nch = (unsigned)(g.n[D] + rows) / rows, ch = item % nch;
+  const unsigned e0 = g.n[0] + 2 * lo - 1, eE = g.n[E] + 2 * lo - 1;
+  const unsigned q = min((item / nch) * 64 + l, e0 * eE - 1);
+  const bool in = (item / nch) * 64 + l < e0 * eE;
+  const int j0 = (int)ch * rows, j1 = min(j0 + rows, g.n[D] + 1);
+  int c[3];
+  c[0] = (int)(q % e0) - lo;
+  c[E] = (int)(q / e0) - lo;
+  c[D] = j0 - 1;
+  const int sD = D == 1 ? g.sy : g.sz;
+  int id = at(g, c[0], c[1], c[2]);
+  double smax = 0.0;
+  // from the cell below the first face, whose own lower face is left out: one copy of the reconstruction's
+  // code, so that a face's result does not depend on where its march begins
+#pragma unroll 1
+  for (int j = j0 - 1; j < j1; ++j, id += sD) {
+    double XL[7], XR[7];
+#pragma unroll
+    for (int v = 0; v < 7; ++v) XL[v] = L.hi[v][l];
+    wave_lds_sync();
+    cell_faces<D, RECON>(g, fa, id, XR, L.hi, L.lo);
+    wave_lds_sync();
+    if (j >= j0 && in) {
+      FaceIn fin;
+      face_load<D>(g, fa, id, fin);
+      smax = fmax(smax, face_solve<D, UCT>(g, fa, id, fin, XL, XR));
+    }
+  }
+  face_report(fa, face_owned<D>(g, c) ? smax : 0.0);
+}
+
+// Swap of a lane pair's values (lanes 2f and 2f + 1, one per side of a face in the adjoint): a DPP quad
+// permutation (1, 0, 3, 2) of the two 32-bit halves, a VALU move; both lanes of a pair are always active
+// together.
+DEV double shfl1(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)b, 0xB1, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), 0xB1, 0xF, 0xF, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -2202,6 +2289,13 @@ __global__ __launch_bounds__(256) void k_c2p_learned_src(GD g, C2PParams cp, C2P
   __shared__ CellLDS S;
   c2p_body<true, true>(g, cp, a, S.t, my_tile());
 }
+__global__ __launch_bounds__(256) void k_c2p_geo(GD g, C2PParams cp, C2PArgs a, const double* cen) {
+  c2p_geo_body<false>(g, cp, a, cen, my_tile(), nullptr);
+}
+__global__ __launch_bounds__(256) void k_c2p_learned_geo(GD g, C2PParams cp, C2PArgs a, const double* cen) {
+  __shared__ C2PGeoLDS L;
+  c2p_geo_body<true>(g, cp, a, cen, my_tile(), &L);
+}
 __global__ __launch_bounds__(256) void kb_c2p(const PatchDesc* __restrict__ P, const Item* __restrict__ it, int nit,
                                               C2PParams cp, C2PArgs a) {
   __shared__ C2PLDS S;
@@ -2240,21 +2334,58 @@ __global__ __launch_bounds__(256) void kb_bcent(const PatchDesc* __restrict__ P,
   }
 }
 
-template <int D, int R>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(R == ASTERX_RECON_WENOZ ? 5 : 4))) void k_face(GD g, FaceArgs fa) {
+template <int MASK>
+__global__ __launch_bounds__(64) void k_geom(GD g, GeomArgs ga) { geom_wave<MASK>(g, ga, my_tile()); }
+// Batches: the wavefronts of a workgroup take items of their own.
+DEV int first_wave_item() { return (int)(blockIdx.x * 4 + (threadIdx.x >> 6)); }
+template <int MASK>
+__global__ __launch_bounds__(256) void kb_geom(const PatchDesc* __restrict__ P, const Item* __restrict__ it, int nit,
+                                               GeomArgs ga) {
+  for (int w = __builtin_amdgcn_readfirstlane(first_wave_item()); w < nit; w += gridDim.x * 4) {
+    const Item m = it[w];
+    const PatchDesc d = P[m.patch];
+    GeomArgs b = ga;
+    b.metric = ga.metric + d.off;
+    b.curv = shifted(ga.curv, d.off);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      b.fa[a] = shifted(ga.fa[a], d.off);
+      b.fb[a] = shifted(ga.fb[a], d.off);
+    }
+    int e[3];
+    geom_box(d.g.n, ga.lo, e);
+    b.zl = geom_planes(e);
+    geom_wave<MASK>(d.g, b, (unsigned)m.tile);
+  }
+}
+
+// 3 wavefronts per SIMD: both sides' states and fluxes of a face are live together (146-168 registers); held
+// at 4 the kernels spill (128^3, PPM: x faces 0.15 -> 0.21 ms, y 0.19 -> 0.24).
+template <int D, int R, bool UCT>
+DEV void face_wave(const GD& g, const FaceArgs& fa, unsigned item, FaceLDS& L) {
+  if constexpr (D == 0) face_wave_x<R, UCT>(g, fa, item, L);
+  else face_wave_yz<D, R, UCT>(g, fa, item, L);
+}
+template <int D, int R, bool UCT>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_face(GD g, FaceArgs fa) {
   __shared__ FaceLDS L;
-  face_body<D, R>(g, fa, my_tile(), L);
+  face_wave<D, R, UCT>(g, fa, my_tile(), L);
+}
+// The three directions in one launch: c0 and c1 x and y items, then the z items.
+template <int R, bool UCT>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_faces(GD g, FaceArgs fa, unsigned c0,
+                                                                                     unsigned c1) {
+  __shared__ FaceLDS L;
+  const unsigned w = blockIdx.x;
+  if (w < c0) face_wave<0, R, UCT>(g, fa, xcd_block(w, c0), L);
+  else if (w < c0 + c1) face_wave<1, R, UCT>(g, fa, xcd_block(w - c0, c1), L);
+  else face_wave<2, R, UCT>(g, fa, xcd_block(w - c0 - c1, gridDim.x - c0 - c1), L);
 }
 template <int D, int R>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_face_uct(GD g, FaceArgs fa) {
-  __shared__ FaceLDS L;
-  face_body<D, R, true>(g, fa, my_tile(), L);
-}
-template <int D, int R>
-__global__ __launch_bounds__(256) void kb_face(const PatchDesc* __restrict__ P, const Item* __restrict__ it, int nit,
-                                               FaceArgs fa) {
-  __shared__ FaceLDS L;
-  for (int w = blockIdx.x; w < nit; w += gridDim.x) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void kb_face(
+    const PatchDesc* __restrict__ P, const Item* __restrict__ it, int nit, FaceArgs fa) {
+  __shared__ FaceLDS L[4];
+  for (int w = __builtin_amdgcn_readfirstlane(first_wave_item()); w < nit; w += gridDim.x * 4) {
     const Item m = it[w];
     const PatchDesc d = P[m.patch];
     FaceArgs b = fa;
@@ -2263,7 +2394,10 @@ __global__ __launch_bounds__(256) void kb_face(const PatchDesc* __restrict__ P, 
     b.A = fa.A + d.off;
     b.bc = fa.bc + d.off;
     b.flux = fa.flux + d.off;
-    face_body<D, R>(d.g, b, (unsigned)m.tile, L);
+    b.fma[D] = shifted(fa.fma[D], d.off);
+    b.fmb[D] = shifted(fa.fmb[D], d.off);
+    wave_lds_sync();  // the previous item's reads come before this one's writes
+    face_wave<D, R, false>(d.g, b, (unsigned)m.tile, L[threadIdx.x >> 6]);
   }
 }
 
@@ -2311,6 +2445,18 @@ __global__ __launch_bounds__(256) void kb_vertex(const PatchDesc* __restrict__ P
 
 __global__ __launch_bounds__(256) void k_edge(GD g, EdgeArgs ea) { edge_body(g, ea, my_tile()); }
 __global__ __launch_bounds__(256) void k_edge_uct(GD g, EdgeArgs ea) { edge_body<true>(g, ea, my_tile()); }
+// Two phases that don't depend on each other in one launch, the first n0 workgroups for the first: the centre
+// field and the gauge quantities before the faces, the divergence and the edges after them.  Small blocks save the
+// launches (16^3 and 32^3: about 3 us each from a graph, 5 eagerly).
+__global__ __launch_bounds__(256) void k_bcent_vertex(GD g, const double* A, double* bc, VertexArgs va, unsigned n0) {
+  if (blockIdx.x < n0) bcent_body(g, A, bc, xcd_block(blockIdx.x, n0));
+  else vertex_body(g, va, xcd_block(blockIdx.x - n0, gridDim.x - n0));
+}
+template <bool UCT>
+__global__ __launch_bounds__(256) void k_div_edge(GD g, DivArgs da, EdgeArgs ea, unsigned n0) {
+  if (blockIdx.x < n0) div_body(g, da, xcd_block(blockIdx.x, n0));
+  else edge_body<UCT>(g, ea, xcd_block(blockIdx.x - n0, gridDim.x - n0));
+}
 __global__ __launch_bounds__(256) void kb_edge(const PatchDesc* __restrict__ P, const Item* __restrict__ it, int nit,
                                                EdgeArgs ea) {
   for (int w = blockIdx.x; w < nit; w += gridDim.x) {
@@ -3171,11 +3317,11 @@ int launched() {
 // use while a stream is being captured into a graph.
 enum {
   KT_PRIM2CON, KT_C2P, KT_FILL, KT_BCENT, KT_FACE_X, KT_FACE_Y, KT_FACE_Z, KT_CELL, KT_VERTEX, KT_EDGE, KT_RK,
-  KT_ZERO, KT_ADJ, KT_TMUNU, KT_INTER, KT_N
+  KT_ZERO, KT_ADJ, KT_TMUNU, KT_INTER, KT_GEOM, KT_N
 };
 const char* const kt_names[KT_N] = {"prim2con", "c2p", "fill_ghosts", "centre_B", "face_x", "face_y",
                                     "face_z", "cell", "vertex", "edge", "rk_stage", "zero", "adjoint", "tmunu",
-                                    "inter_level"};
+                                    "inter_level", "geometry"};
 struct Pending {
   hipEvent_t a, b;
   int kind;
@@ -3220,8 +3366,8 @@ int timed(int kind, hipStream_t s, F&& launch) {
 // ---------------------------------------------------------------------------------------
 // Launch targets.  A single block launches one workgroup per tile of each phase; a batch
 // of patches launches a persistent grid over that phase's (patch, tile) work list.
-enum { PH_P2C, PH_C2P, PH_FILL, PH_BCENT, PH_FACE, PH_CELL, PH_VERTEX, PH_EDGE, PH_RK,
-       PH_N };
+enum { PH_P2C, PH_C2P, PH_FILL, PH_BCENT, PH_FACEX, PH_FACEY, PH_FACEZ, PH_CELL, PH_VERTEX, PH_EDGE,
+       PH_RK, PH_GEOM, PH_N };
 
 unsigned host_tile_blocks(const GD& g) {
   return (unsigned)(((g.n[0] + CTX - 1) / CTX) * ((g.n[1] + CTY - 1) / CTY) * ((g.n[2] + CTZ - 1) / CTZ));
@@ -3241,9 +3387,13 @@ unsigned tiles_for(int phase, const GD& g) {
       const long long cnt = G * E1 * E2 + (long long)g.n[0] * G * E2 + (long long)g.n[0] * g.n[1] * G;
       return (unsigned)((cnt + 255) / 256);
     }
-    case PH_FACE:
-      for (int a = 0; a < 3; ++a) e[a] = g.n[a] + 1;
-      return face_tiles(e);
+    // as in batches (single blocks choose their own march lengths)
+    case PH_FACEX:
+    case PH_FACEY:
+    case PH_FACEZ:
+      return face_items(g.n, phase - PH_FACEX, 1, FACE_BATCH_ROWS);
+    case PH_GEOM:  // of one component
+      return geom_items(g, 1, 10, geom_rows<GM_Z>());
     case PH_VERTEX:
       for (int a = 0; a < 3; ++a) e[a] = g.n[a] + 2;
       return lin_blocks(e);
@@ -3283,42 +3433,66 @@ unsigned bgrid(const asterx_batch* b, int phase) {
                          : 0)                                                                                \
      : timed(KT, s, [&] { hipLaunchKernelGGL(KS, dim3(tiles_for(PHASE, g)), dim3(256), 0, s, g, __VA_ARGS__); }))
 
+// Phases whose items are wavefronts: single blocks launch workgroups of one wavefront (count of them), batches
+// persistent workgroups of four whose wavefronts walk the work list.
+#define RUN_WAVES(KT, PHASE, COUNT, KS, KB, ...)                                                              \
+  (b ? (b->nitems[PHASE] ? timed(KT, s,                                                                      \
+                                 [&] {                                                                       \
+                                   const int nw = (b->nitems[PHASE] + 3) / 4;                                \
+                                   hipLaunchKernelGGL(KB, dim3(nw < b->blocks ? nw : b->blocks), dim3(256), 0, s, \
+                                                      b->d_patches, b->d_items[PHASE], b->nitems[PHASE],     \
+                                                      __VA_ARGS__);                                          \
+                                 })                                                                          \
+                         : 0)                                                                                \
+     : timed(KT, s, [&] { hipLaunchKernelGGL(KS, dim3(COUNT), dim3(64), 0, s, g, __VA_ARGS__); }))
+
+template <int D, int R>
+int face_launch(const GD& g, const asterx_batch* b, FaceArgs fa, bool uct, hipStream_t s) {
+  const int lo = uct ? 3 : 1;
+  fa.rows[D] = b ? FACE_BATCH_ROWS : face_rows(g.n, D, lo, face_march<R>());
+  const unsigned count = b ? 0 : face_items(g.n, D, lo, fa.rows[D]);
+  if (uct) return timed(KT_FACE_X + D, s, [&] { hipLaunchKernelGGL((k_face<D, R, true>), dim3(count), dim3(64), 0, s, g, fa); });
+  return RUN_WAVES(KT_FACE_X + D, PH_FACEX + D, count, (k_face<D, R, false>), (kb_face<D, R>), fa);
+}
+
+template <int D>
+int faces(const GD& g, const asterx_batch* b, const FaceArgs& fa, bool uct, hipStream_t s) {
+  if (fa.recon == ASTERX_RECON_MINMOD) return face_launch<D, ASTERX_RECON_MINMOD>(g, b, fa, uct, s);
+  if (fa.recon == ASTERX_RECON_PPM) return face_launch<D, ASTERX_RECON_PPM>(g, b, fa, uct, s);
+  if (fa.recon == ASTERX_RECON_MP5) return face_launch<D, ASTERX_RECON_MP5>(g, b, fa, uct, s);
+  return face_launch<D, ASTERX_RECON_WENOZ>(g, b, fa, uct, s);
+}
+
+// All directions in one launch: no direction waits for another's last wavefronts (RK4 steps with the directions
+// in launches of their own and in one: 64^3, PPM, 0.811 and 0.728 ms; 97 x 61 x 45, MP5, upwind CT, 1.194 and
+// 1.050; 96^3, WENO-Z, 2.49 and 2.37; 128^3, PPM, 5.06 and 5.02).
 template <int R>
-int faces_r(const GD& g, const asterx_batch* b, const FaceArgs& fa, hipStream_t s) {
-  int rc;
-  if ((rc = RUN_PHASE(KT_FACE_X, PH_FACE, (k_face<0, R>), (kb_face<0, R>), fa))) return rc;
-  if ((rc = RUN_PHASE(KT_FACE_Y, PH_FACE, (k_face<1, R>), (kb_face<1, R>), fa))) return rc;
-  return RUN_PHASE(KT_FACE_Z, PH_FACE, (k_face<2, R>), (kb_face<2, R>), fa);
+int faces_joint(const GD& g, FaceArgs fa, bool uct, hipStream_t s) {
+  const int lo = uct ? 3 : 1;
+  unsigned c[3];
+  for (int d = 0; d < 3; ++d) {
+    fa.rows[d] = face_rows(g.n, d, lo, face_march<R>());
+    c[d] = face_items(g.n, d, lo, fa.rows[d]);
+  }
+  const dim3 all(c[0] + c[1] + c[2]);
+  if (uct) hipLaunchKernelGGL((k_faces<R, true>), all, dim3(64), 0, s, g, fa, c[0], c[1]);
+  else hipLaunchKernelGGL((k_faces<R, false>), all, dim3(64), 0, s, g, fa, c[0], c[1]);
+  return launched();
+}
+int all_faces(const GD& g, const FaceArgs& fa, bool uct, hipStream_t s) {
+  if (fa.recon == ASTERX_RECON_MINMOD) return faces_joint<ASTERX_RECON_MINMOD>(g, fa, uct, s);
+  if (fa.recon == ASTERX_RECON_PPM) return faces_joint<ASTERX_RECON_PPM>(g, fa, uct, s);
+  if (fa.recon == ASTERX_RECON_MP5) return faces_joint<ASTERX_RECON_MP5>(g, fa, uct, s);
+  return faces_joint<ASTERX_RECON_WENOZ>(g, fa, uct, s);
 }
 
-// Upwind CT (single blocks): faces over transverse indices [-3, n+1].
-template <int R>
-int faces_uct_r(const GD& g, const FaceArgs& fa, hipStream_t s) {
-  int rc;
-  auto tiles = [&](int D) {
-    int e[3] = {g.n[0] + 5, g.n[1] + 5, g.n[2] + 5};
-    e[D] = g.n[D] + 1;
-    return face_tiles(e);
-  };
-  if ((rc = timed(KT_FACE_X, s, [&] { hipLaunchKernelGGL((k_face_uct<0, R>), dim3(tiles(0)), dim3(256), 0, s, g, fa); })))
-    return rc;
-  if ((rc = timed(KT_FACE_Y, s, [&] { hipLaunchKernelGGL((k_face_uct<1, R>), dim3(tiles(1)), dim3(256), 0, s, g, fa); })))
-    return rc;
-  return timed(KT_FACE_Z, s, [&] { hipLaunchKernelGGL((k_face_uct<2, R>), dim3(tiles(2)), dim3(256), 0, s, g, fa); });
-}
-
-int faces_uct(const GD& g, const FaceArgs& fa, int recon, hipStream_t s) {
-  if (recon == ASTERX_RECON_MINMOD) return faces_uct_r<ASTERX_RECON_MINMOD>(g, fa, s);
-  if (recon == ASTERX_RECON_PPM) return faces_uct_r<ASTERX_RECON_PPM>(g, fa, s);
-  if (recon == ASTERX_RECON_MP5) return faces_uct_r<ASTERX_RECON_MP5>(g, fa, s);
-  return faces_uct_r<ASTERX_RECON_WENOZ>(g, fa, s);
-}
-
-int faces(const GD& g, const asterx_batch* b, const FaceArgs& fa, int recon, hipStream_t s) {
-  if (recon == ASTERX_RECON_MINMOD) return faces_r<ASTERX_RECON_MINMOD>(g, b, fa, s);
-  if (recon == ASTERX_RECON_PPM) return faces_r<ASTERX_RECON_PPM>(g, b, fa, s);
-  if (recon == ASTERX_RECON_MP5) return faces_r<ASTERX_RECON_MP5>(g, b, fa, s);
-  return faces_r<ASTERX_RECON_WENOZ>(g, b, fa, s);
+// Interpolated spacetime data of the sets in MASK.
+template <int MASK>
+int geometry(const GD& g, const asterx_batch* b, GeomArgs ga, hipStream_t s) {
+  int e[3];
+  geom_box(g.n, ga.lo, e);
+  ga.zl = geom_planes(e);
+  return RUN_WAVES(KT_GEOM, PH_GEOM, geom_items(g, ga.lo, (MASK & GM_C) ? 16 : 10, geom_rows<MASK>()), (k_geom<MASK>), (kb_geom<MASK>), ga);
 }
 
 // ---- the phases, shared by the single-block and the batched entry points ----
@@ -3420,11 +3594,15 @@ int do_bcent(const GD& g, const double* A, double* bc, hipStream_t s) {
   return RUN_PHASE(KT_BCENT, PH_BCENT, k_bcent, kb_bcent, A, bc);
 }
 
-// src (single blocks): densitized sources stored by the recovery with sources; the cell phase is
-// then the divergence kernel instead of the cell kernel.
+// src (single blocks): densitized sources stored by a recovery with sources; the cell phase is
+// then the divergence kernel instead of the cell kernel.  The face metric comes from geo (all directions,
+// as stored by asterx_geometry), for x faces from xfm (as stored by asterx_c2p_src), or is interpolated
+// here into parts of the workspace that hold nothing at that time: the fluxes of directions not yet done,
+// the gauge quantities (written after the faces) and, under flux CT, the nine fields of upwind CT.
 int do_rhs(const GD& g, const asterx_batch* b, const asterx_params* p, const double* metric, const double* curv,
            const double* prim, const double* A, const double* psi, double dt_max, double* rhs, double* red,
-           double* ws, hipStream_t s, const Combine& cmb = Combine{}, const double* src = nullptr) {
+           double* ws, hipStream_t s, const Combine& cmb = Combine{}, const double* src = nullptr,
+           const double* xfm = nullptr, const double* geo = nullptr) {
   int rc;
   double* bc = ws;
   double* flux = ws + 3 * g.N;
@@ -3432,10 +3610,69 @@ int do_rhs(const GD& g, const asterx_batch* b, const asterx_params* p, const dou
   double* fp = ws + 25 * g.N;
   double* apm = ws + 28 * g.N;
   const bool uct = p->ct == ASTERX_CT_UCT;
-  if ((rc = RUN_PHASE(KT_BCENT, PH_BCENT, k_bcent, kb_bcent, A, bc))) return rc;
+  // With stored geometry phases share launches (kernel timing keeps them apart: its classes are phases).
+  const bool joint = geo && !b && !g_timing, lorenz = p->gauge == ASTERX_GAUGE_LORENZ;
+  const VertexArgs va{metric, A, psi, ga, fp};
+  if (joint && lorenz) {
+    const unsigned n0 = tiles_for(PH_BCENT, g), n1 = tiles_for(PH_VERTEX, g);
+    hipLaunchKernelGGL(k_bcent_vertex, dim3(n0 + n1), dim3(256), 0, s, g, A, bc, va, n0);
+    rc = launched();
+  } else {
+    rc = RUN_PHASE(KT_BCENT, PH_BCENT, k_bcent, kb_bcent, A, bc);
+  }
+  if (rc) return rc;
   FaceArgs fa{metric, prim, A, bc, flux, red, p->gamma, p->weno_eps, p->weno_q, p->gamma / (p->gamma - 1.0),
-              p->recon, p->speeds, p->riemann, apm, (src && !uct) ? src + 4 * g.N : nullptr};
-  if ((rc = uct ? faces_uct(g, fa, p->recon, s) : faces(g, b, fa, p->recon, s))) return rc;
+              p->recon, p->speeds, p->riemann, apm, {nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr}, {1, 1, 1}, false};
+  GeomArgs gm{metric, nullptr, {nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr}, nullptr, uct ? 3 : 1, 0};
+  auto put = [&](int d, int f0, int f1) {  // components 0..6 into workspace fields from f0, 7..9 from f1
+    gm.fa[d] = ws + (size_t)f0 * g.N;
+    gm.fb[d] = ws + (size_t)f1 * g.N;
+    fa.fma[d] = gm.fa[d];
+    fa.fmb[d] = gm.fb[d];
+  };
+  // workspace fields: x fluxes 3..9, y 10..16, z 17..23, gauge 24..27, upwind CT 28..30 (x), 31..33 (y), 34..36 (z)
+  bool later_z = false;
+  if (geo) {
+    for (int d = 0; d < 3; ++d) {
+      fa.fma[d] = geo + (size_t)(10 * d) * g.N;
+      fa.fmb[d] = fa.fma[d] + 7 * g.N;
+    }
+  } else if (uct) {
+    put(0, 10, 17);
+    put(1, 20, 34);
+    if ((rc = geometry<GM_X | GM_Y>(g, b, gm, s))) return rc;  // z faces gather theirs: no ten fields are free then
+  } else if (xfm) {
+    fa.xown = true;
+    fa.fma[0] = xfm;
+    fa.fmb[0] = xfm + 7 * g.N;
+    put(1, 17, 34);
+    put(2, 24, 31);
+    if ((rc = geometry<GM_Y | GM_Z>(g, b, gm, s))) return rc;
+  } else {
+    put(0, 24, 31);
+    put(1, 17, 34);
+    later_z = true;
+    if ((rc = geometry<GM_X | GM_Y>(g, b, gm, s))) return rc;
+  }
+  if (joint) {
+    if ((rc = all_faces(g, fa, uct, s))) return rc;
+  } else {
+    if ((rc = faces<0>(g, b, fa, uct, s))) return rc;
+    if ((rc = faces<1>(g, b, fa, uct, s))) return rc;
+    if (later_z) {
+      put(2, 24, 31);
+      if ((rc = geometry<GM_Z>(g, b, gm, s))) return rc;
+    }
+    if ((rc = faces<2>(g, b, fa, uct, s))) return rc;
+  }
+  EdgeArgs ea{metric, psi, flux, ga, fp, rhs, p->xi / dt_max, p->gauge, cmb, apm};
+  if (joint) {
+    const DivArgs da{src, flux, A, rhs, red, cmb};
+    const unsigned n0 = box_blocks<64, 4>(g.n), n1 = tiles_for(PH_EDGE, g);
+    if (uct) hipLaunchKernelGGL(k_div_edge<true>, dim3(n0 + n1), dim3(256), 0, s, g, da, ea, n0);
+    else hipLaunchKernelGGL(k_div_edge<false>, dim3(n0 + n1), dim3(256), 0, s, g, da, ea, n0);
+    return launched();
+  }
   if (src) {
     const DivArgs da{src, flux, A, rhs, red, cmb};
     if ((rc = timed(KT_CELL, s, [&] {
@@ -3446,11 +3683,7 @@ int do_rhs(const GD& g, const asterx_batch* b, const asterx_params* p, const dou
     CellArgs ca{metric, curv, prim, A, bc, flux, rhs, red, p->gamma, cmb};
     if ((rc = RUN_PHASE(KT_CELL, PH_CELL, k_cell, kb_cell, ca))) return rc;
   }
-  if (p->gauge == ASTERX_GAUGE_LORENZ) {
-    VertexArgs va{metric, A, psi, ga, fp};
-    if ((rc = RUN_PHASE(KT_VERTEX, PH_VERTEX, k_vertex, kb_vertex, va))) return rc;
-  }
-  EdgeArgs ea{metric, psi, flux, ga, fp, rhs, p->xi / dt_max, p->gauge, cmb, apm};
+  if (lorenz && (rc = RUN_PHASE(KT_VERTEX, PH_VERTEX, k_vertex, kb_vertex, va))) return rc;
   if (uct)
     return timed(KT_EDGE, s, [&] {
       hipLaunchKernelGGL(k_edge_uct, dim3(tiles_for(PH_EDGE, g)), dim3(256), 0, s, g, ea);
@@ -3611,7 +3844,7 @@ int asterx_timing_reset(void) {
 
 const char* asterx_timing_name(int32_t k) { return (k >= 0 && k < KT_N) ? kt_names[k] : ""; }
 
-int asterx_version(void) { return 7; }
+int asterx_version(void) { return 8; }
 
 const char* asterx_last_error(void) { return g_err.c_str(); }
 
@@ -3757,7 +3990,65 @@ int asterx_rhs_rk_src(const asterx_grid* gr, const asterx_params* p, const doubl
   Combine cmb;
   if ((rc = make_combine(nout, outs, g.N, ins, nin, 6, cmb))) return rc;
   return do_rhs(g, nullptr, p, metric, nullptr, prim, A, psi, dt_max, nullptr, red, (double*)workspace,
-                (hipStream_t)stream, cmb, src);
+                (hipStream_t)stream, cmb, src, p->ct == ASTERX_CT_UCT ? nullptr : src + 4 * g.N);
+}
+
+int asterx_geometry(const asterx_grid* gr, const asterx_params* p, const double* metric, const double* curv, double* geo,
+                    void* stream) {
+  int rc;
+  if ((rc = check_params(p)) || (rc = check_grid(gr, 3))) return rc;
+  if (p->ct == ASTERX_CT_UCT && gr->ng < 4) return fail(ASTERX_EARG, "geometry: upwind CT needs ng >= 4");
+  if (!metric || !curv || !geo) return fail(ASTERX_EARG, "geometry: NULL array");
+  GD g = make_gd(gr);
+  GeomArgs ga{metric, curv, {}, {}, geo + (size_t)GEO_CEN * g.N, p->ct == ASTERX_CT_UCT ? 3 : 1, 0};
+  for (int d = 0; d < 3; ++d) {
+    ga.fa[d] = geo + (size_t)(10 * d) * g.N;
+    ga.fb[d] = ga.fa[d] + 7 * g.N;
+  }
+  return geometry<GM_X | GM_Y | GM_Z | GM_C>(g, nullptr, ga, (hipStream_t)stream);
+}
+
+int asterx_c2p_geo(const asterx_grid* gr, const asterx_params* p, const double* geo, const double* A, double* cons,
+                   double* prim, uint8_t* flags, asterx_c2p_stats* stats, const asterx_mlp* mlp, double* src,
+                   void* stream) {
+  int rc;
+  if ((rc = check_grid(gr, 2)) || (rc = check_params(p))) return rc;
+  if (!geo || !A || !prim || !cons || !src) return fail(ASTERX_EARG, "c2p_geo: NULL array");
+  mlpd::Stdz z{};
+  if (mlp) {
+    if (!mlp->params) return fail(ASTERX_EARG, "c2p_geo: NULL network parameters");
+    if ((rc = make_stdz(mlp, z, "c2p_geo"))) return rc;
+  }
+  GD g = make_gd(gr);
+  hipStream_t s = (hipStream_t)stream;
+  const C2PParams cp = make_c2p_params(p);
+  const C2PArgs a{nullptr, A, cons, prim, flags, (unsigned long long*)stats, mlp ? mlp->params : nullptr, z, nullptr, src};
+  const double* cen = geo + (size_t)GEO_CEN * g.N;
+  return timed(KT_C2P, s, [&] {
+    if (mlp)
+      hipLaunchKernelGGL(k_c2p_learned_geo, dim3(lin_blocks(g.n)), dim3(256), 0, s, g, cp, a, cen);
+    else
+      hipLaunchKernelGGL(k_c2p_geo, dim3(lin_blocks(g.n)), dim3(256), 0, s, g, cp, a, cen);
+  });
+}
+
+int asterx_rhs_rk_geo(const asterx_grid* gr, const asterx_params* p, const double* metric, const double* geo,
+                      const double* prim, const double* A, const double* psi, const double* src, double dt_max,
+                      int32_t nout, const asterx_rk_out* outs, double* red, void* workspace, size_t ws_bytes,
+                      void* stream) {
+  int rc;
+  if ((rc = check_params(p)) || (rc = check_grid(gr, 3))) return rc;
+  if (p->ct == ASTERX_CT_UCT && gr->ng < 4) return fail(ASTERX_EARG, "rhs_rk_geo: upwind CT needs ng >= 4");
+  if (!metric || !geo || !prim || !A || !psi || !src || !workspace) return fail(ASTERX_EARG, "rhs_rk_geo: NULL array");
+  if (ws_bytes < asterx_rhs_workspace_size(gr)) return fail(ASTERX_EARG, "rhs_rk_geo: workspace too small");
+  if (!(dt_max > 0.0)) return fail(ASTERX_EARG, "rhs_rk_geo: dt_max must be > 0");
+  GD g = make_gd(gr);
+  const double* ins[7] = {metric, prim, A, psi, src, (const double*)workspace, geo};
+  const size_t nin[7] = {10 * g.N, 5 * g.N, 3 * g.N, g.N, 4 * g.N, ws_bytes / sizeof(double), ASTERX_GEO_FIELDS * g.N};
+  Combine cmb;
+  if ((rc = make_combine(nout, outs, g.N, ins, nin, 7, cmb))) return rc;
+  return do_rhs(g, nullptr, p, metric, nullptr, prim, A, psi, dt_max, nullptr, red, (double*)workspace,
+                (hipStream_t)stream, cmb, src, nullptr, geo);
 }
 
 int asterx_rhs_rk_noalloc(const asterx_grid* gr, const asterx_params* p, const double* metric, const double* curv,

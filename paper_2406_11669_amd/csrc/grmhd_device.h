@@ -658,6 +658,35 @@ DEV T wenoz_face(T m2, T m1, T c0, T p1, T p2, double eps, double q) {
   return (w0 * q0 + w1 * q1 + w2 * q2) / (6.0 * (w0 + w1 + w2));
 }
 
+// Both face values of the middle cell: hi = wenoz_face of the stencil, lo = wenoz_face of its mirror image,
+// which swaps the outer indicators; the ratios tau / (beta + eps) serve both.
+DEV void wenoz_cell(double m2, double m1, double c0, double p1, double p2, double eps, double q, double& lo,
+                    double& hi) {
+  const double t13 = 13.0 / 12.0;
+  const double e0 = m2 - 2.0 * m1 + c0, f0 = m2 - 4.0 * m1 + 3.0 * c0;
+  const double e1 = m1 - 2.0 * c0 + p1, f1 = m1 - p1;
+  const double e2 = c0 - 2.0 * p1 + p2, f2 = 3.0 * c0 - 4.0 * p1 + p2;
+  const double b0 = t13 * e0 * e0 + 0.25 * f0 * f0;
+  const double b1 = t13 * e1 * e1 + 0.25 * f1 * f1;
+  const double b2 = t13 * e2 * e2 + 0.25 * f2 * f2;
+  const double tau = fabs(b0 - b2);
+  double r0 = tau / (b0 + eps), r1 = tau / (b1 + eps), r2 = tau / (b2 + eps);
+  if (q != 1.0) {
+    r0 = pow(r0, q);
+    r1 = pow(r1, q);
+    r2 = pow(r2, q);
+  }
+  const double a1 = 0.6 * (1.0 + r1);
+  {
+    const double w0 = 0.1 * (1.0 + r0), w2 = 0.3 * (1.0 + r2);
+    const double q0 = 2.0 * m2 - 7.0 * m1 + 11.0 * c0, q1 = -m1 + 5.0 * c0 + 2.0 * p1, q2 = 2.0 * c0 + 5.0 * p1 - p2;
+    hi = (w0 * q0 + a1 * q1 + w2 * q2) / (6.0 * (w0 + a1 + w2));
+  }
+  const double w0 = 0.1 * (1.0 + r2), w2 = 0.3 * (1.0 + r0);
+  const double q0 = 2.0 * p2 - 7.0 * p1 + 11.0 * c0, q1 = -p1 + 5.0 * c0 + 2.0 * m1, q2 = 2.0 * c0 + 5.0 * m1 - m2;
+  lo = (w0 * q0 + a1 * q1 + w2 * q2) / (6.0 * (w0 + a1 + w2));
+}
+
 // A linear form sum_q c_q a_q over a 5-point stencil, with its value: the piecewise-linear
 // reconstructions evaluated on it (selections follow the value) give their gradient exactly.
 struct Lin5 {
@@ -717,6 +746,27 @@ DEV T mp5_face(T m2, T m1, T c0, T p1, T p2) {
   T f_max = tmin(tmax(tmax(c0, p1), f_md), tmax(tmax(c0, f_ul), f_lc));
   T lim = f_or + mm(f_min - f_or, f_max - f_or);
   return val(f_or - c0) * val(f_or - f_mp) <= 0.0 ? f_or : lim;
+}
+
+// Both face values of the middle cell: hi = mp5_face of the stencil, lo = mp5_face of its mirror image, which
+// swaps the outer curvatures and with them the two bounds' minmods.
+DEV double mp5_side(double f_or, double c0, double m1, double p1, double dl, double dr) {
+  const double alpha = 4.0;
+  const double f_mp = c0 + mm(p1 - c0, alpha * (c0 - m1));
+  const double f_ul = c0 + alpha * (c0 - m1);
+  const double f_md = 0.5 * (c0 + p1) - 0.5 * dr;
+  const double f_lc = c0 + 0.5 * (c0 - m1) + (4.0 / 3.0) * dl;
+  const double f_min = tmax(tmin(tmin(c0, p1), f_md), tmin(tmin(c0, f_ul), f_lc));
+  const double f_max = tmin(tmax(tmax(c0, p1), f_md), tmax(tmax(c0, f_ul), f_lc));
+  const double lim = f_or + mm(f_min - f_or, f_max - f_or);
+  return (f_or - c0) * (f_or - f_mp) <= 0.0 ? f_or : lim;
+}
+DEV void mp5_cell(double m2, double m1, double c0, double p1, double p2, double& lo, double& hi) {
+  const double d_m = m2 - 2.0 * m1 + c0, d_0 = m1 - 2.0 * c0 + p1, d_p = c0 - 2.0 * p1 + p2;
+  const double dr = minmod4(4.0 * d_0 - d_p, 4.0 * d_p - d_0, d_0, d_p);
+  const double dl = minmod4(4.0 * d_0 - d_m, 4.0 * d_m - d_0, d_0, d_m);
+  hi = mp5_side((2.0 * m2 - 13.0 * m1 + 47.0 * c0 + 27.0 * p1 - 3.0 * p2) * (1.0 / 60.0), c0, m1, p1, dl, dr);
+  lo = mp5_side((2.0 * p2 - 13.0 * p1 + 47.0 * c0 + 27.0 * m1 - 3.0 * m2) * (1.0 / 60.0), c0, p1, m1, dr, dl);
 }
 
 // ---------------------------------------------------------------------------------------
