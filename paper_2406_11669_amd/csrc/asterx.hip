@@ -1940,53 +1940,87 @@ struct InterArgs {
 
 DEV int fdiv2(int f) { return f >= 0 ? f / 2 : -((1 - f) / 2); }
 
-// 1-D prolongation stencil: first coarse index, count and weights
-DEV int pstencil(int f, int c0, int vertex, int& first, double w[4]) {
-  if (vertex) {
-    if ((f & 1) == 0) {
-      first = c0 + f / 2;
-      w[0] = 1.0;
-      return 1;
-    }
-    first = c0 + fdiv2(f) - 1;
-    w[0] = -1.0 / 16.0;
-    w[1] = 9.0 / 16.0;
-    w[2] = 9.0 / 16.0;
-    w[3] = -1.0 / 16.0;
-    return 4;
+// The two children along x of one coarse point, at fine point (f0, f1, f2), f0 even: one 16-byte store (rows start
+// at any 8-byte address; against single children's, 16 bytes apart: 11.6 and 12.5 us), or the one in the box.
+typedef double pair8 __attribute__((ext_vector_type(2), aligned(8)));
+DEV void store_children(const InterArgs& a, double* o, int f0, int f1, int f2, double c0, double c1) {
+  if (f1 < a.lo[1] || f1 > a.hi[1] || f2 < a.lo[2] || f2 > a.hi[2]) return;
+  double* p = o + at(a.gf, f0, f1, f2);
+  if (f0 >= a.lo[0] && f0 < a.hi[0]) {
+    *(pair8*)p = pair8{c0, c1};
+  } else if (f0 >= a.lo[0] && f0 <= a.hi[0]) {
+    p[0] = c0;
+  } else if (f0 + 1 >= a.lo[0] && f0 < a.hi[0]) {
+    p[1] = c1;
   }
-  const int child = f - 2 * fdiv2(f);
-  first = c0 + fdiv2(f) - 1;
-  w[0] = child ? -1.0 / 8.0 : 1.0 / 8.0;
-  w[1] = 1.0;
-  w[2] = child ? 1.0 / 8.0 : -1.0 / 8.0;
-  return 3;
 }
 
-// Fields vertex-centred along at least one axis: one thread per fine point.
+// Both children of a coarse point along one axis from its 1-D stencil u (cell: c-1, c, c+1; vertex: c-1 .. c+2,
+// the first child on the point itself).
+template <bool VERTEX>
+DEV void children(const double* u, double& c0, double& c1) {
+  if constexpr (VERTEX) {
+    c0 = u[1];
+    c1 = (9.0 * (u[1] + u[2]) - (u[0] + u[3])) * (1.0 / 16.0);
+  } else {
+    const double h = (u[2] - u[0]) * 0.125;
+    c0 = u[1] - h;
+    c1 = u[1] + h;
+  }
+}
+
+// Fields vertex-centred along at least one axis (bits of STAG): one thread per coarse point, its eight children by
+// passes along x, y and z, the children inside the fine box stored.  The stencils reach from c - 1 to c + 2 at most,
+// also where a box ends on a first child (the reach that is checked on the host).  Eight children share 36 to 64
+// loads; one thread per child with run-time stencils took up to 64 for each (134^3 points: 50 us per field, now 12).
+template <int STAG>
 DEV void prolong_body(const InterArgs& a, unsigned tile) {
-  const int e[3] = {a.hi[0] - a.lo[0] + 1, a.hi[1] - a.lo[1] + 1, a.hi[2] - a.lo[2] + 1};
+  constexpr bool VX = STAG & 1, VY = STAG & 2, VZ = STAG & 4;
+  constexpr int NX = VX ? 4 : 3, NY = VY ? 4 : 3, NZ = VZ ? 4 : 3;
+  int pl[3], e[3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    pl[d] = a.c0[d] + fdiv2(a.lo[d]);
+    e[d] = a.c0[d] + fdiv2(a.hi[d]) - pl[d] + 1;
+  }
   int i, j, k;
   if (!lin_at(e, tile, threadIdx.x, i, j, k)) return;
-  const int f[3] = {a.lo[0] + i, a.lo[1] + j, a.lo[2] + k};
-  int first[3], n[3];
-  double w[3][4];
-#pragma unroll
-  for (int d = 0; d < 3; ++d) n[d] = pstencil(f[d], a.c0[d], a.stag[d], first[d], w[d]);
+  const int cc[3] = {pl[0] + i, pl[1] + j, pl[2] + k};
+  const int id = at(a.gc, cc[0] - 1, cc[1] - 1, cc[2] - 1);
+  const int f[3] = {2 * (cc[0] - a.c0[0]), 2 * (cc[1] - a.c0[1]), 2 * (cc[2] - a.c0[2])};
   for (int q = 0; q < a.nf; ++q) {
     const double* c = a.src + (size_t)q * a.gc.N;
-    double sum = 0.0;
-    for (int r = 0; r < n[2]; ++r)
-      for (int p2 = 0; p2 < n[1]; ++p2)
-        for (int p1 = 0; p1 < n[0]; ++p1)
-          sum += w[0][p1] * w[1][p2] * w[2][r] * c[at(a.gc, first[0] + p1, first[1] + p2, first[2] + r)];
-    a.dst[(size_t)q * a.gf.N + at(a.gf, f[0], f[1], f[2])] = sum;
+    double z[4][NZ];  // x and y children, planes
+#pragma unroll
+    for (int r = 0; r < NZ; ++r) {
+      double y[2][NY];
+#pragma unroll
+      for (int p = 0; p < NY; ++p) {
+        double u[NX];
+#pragma unroll
+        for (int m = 0; m < NX; ++m) u[m] = c[id + m + p * a.gc.sy + r * a.gc.sz];
+        children<VX>(u, y[0][p], y[1][p]);
+      }
+      children<VY>(y[0], z[0][r], z[2][r]);
+      children<VY>(y[1], z[1][r], z[3][r]);
+    }
+    double* o = a.dst + (size_t)q * a.gf.N;
+#pragma unroll
+    for (int h = 0; h < 4; h += 2) {
+      double l[2], r[2];
+      children<VZ>(z[h], l[0], l[1]);
+      children<VZ>(z[h + 1], r[0], r[1]);
+#pragma unroll
+      for (int m = 0; m < 2; ++m) store_children(a, o, f[0], f[1] + (h >> 1), f[2] + m, l[m], r[m]);
+    }
   }
 }
 
 // Cell fields: one thread per coarse parent of the fine box; the 27 parent-centred values, the fallback
-// decision and all 8 children computed once, the children inside the box stored.
-DEV void prolong_cells_body(const InterArgs& a, unsigned tile) {
+// decision and all 8 children computed once, the children inside the box stored (134^3 points, five fields: 40 us,
+// 2.4 TB/s of stores; the children by axis passes as above would take 37 us, but round a child that lies on the
+// extremes differently, and with it the fallback).
+DEV void prolong_cells_body(const InterArgs& a, unsigned tile, int q) {
   int pl[3], e[3];
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
@@ -1997,51 +2031,46 @@ DEV void prolong_cells_body(const InterArgs& a, unsigned tile) {
   if (!lin_at(e, tile, threadIdx.x, i, j, k)) return;
   const int cc[3] = {pl[0] + i, pl[1] + j, pl[2] + k};
   const size_t Nc = a.gc.N, Nf = a.gf.N;
-  for (int q = 0; q < a.nf; ++q) {
-    const double* c = a.src + (size_t)q * Nc;
-    double u[27];
+  const double* c = a.src + (size_t)q * Nc;
+  double u[27];
 #pragma unroll
-    for (int r = 0; r < 27; ++r) u[r] = c[at(a.gc, cc[0] - 1 + r % 3, cc[1] - 1 + (r / 3) % 3, cc[2] - 1 + r / 9)];
-    double mn = u[13], mx = u[13];
+  for (int r = 0; r < 27; ++r) u[r] = c[at(a.gc, cc[0] - 1 + r % 3, cc[1] - 1 + (r / 3) % 3, cc[2] - 1 + r / 9)];
+  double mn = u[13], mx = u[13];
 #pragma unroll
-    for (int r = 0; r < 27; ++r) {
-      mn = fmin(mn, u[r]);
-      mx = fmax(mx, u[r]);
-    }
-    double ch[8];
-    bool fall = false;
-#pragma unroll
-    for (int h = 0; h < 8; ++h) {
-      const int cx = h & 1, cy = (h >> 1) & 1, cz = h >> 2;
-      const double wx[3] = {cx ? -0.125 : 0.125, 1.0, cx ? 0.125 : -0.125};
-      const double wy[3] = {cy ? -0.125 : 0.125, 1.0, cy ? 0.125 : -0.125};
-      const double wz[3] = {cz ? -0.125 : 0.125, 1.0, cz ? 0.125 : -0.125};
-      double sum = 0.0;
-#pragma unroll
-      for (int r = 0; r < 3; ++r)
-#pragma unroll
-        for (int p2 = 0; p2 < 3; ++p2)
-#pragma unroll
-          for (int p1 = 0; p1 < 3; ++p1) sum += wx[p1] * wy[p2] * wz[r] * u[p1 + 3 * p2 + 9 * r];
-      ch[h] = sum;
-      fall = fall || sum < mn || sum > mx;
-    }
-    if (fall) {
-      const double uc = u[13];
-      const double sx = mm(u[14] - uc, uc - u[12]), sy = mm(u[16] - uc, uc - u[10]), sz = mm(u[22] - uc, uc - u[4]);
-#pragma unroll
-      for (int h = 0; h < 8; ++h)
-        ch[h] = uc + ((h & 1) ? 0.25 : -0.25) * sx + (((h >> 1) & 1) ? 0.25 : -0.25) * sy + ((h >> 2) ? 0.25 : -0.25) * sz;
-    }
-    double* o = a.dst + (size_t)q * Nf;
-#pragma unroll
-    for (int h = 0; h < 8; ++h) {
-      const int f0 = 2 * (cc[0] - a.c0[0]) + (h & 1), f1 = 2 * (cc[1] - a.c0[1]) + ((h >> 1) & 1),
-                f2 = 2 * (cc[2] - a.c0[2]) + (h >> 2);
-      if (f0 >= a.lo[0] && f0 <= a.hi[0] && f1 >= a.lo[1] && f1 <= a.hi[1] && f2 >= a.lo[2] && f2 <= a.hi[2])
-        o[at(a.gf, f0, f1, f2)] = ch[h];
-    }
+  for (int r = 0; r < 27; ++r) {
+    mn = fmin(mn, u[r]);
+    mx = fmax(mx, u[r]);
   }
+  double ch[8];
+  bool fall = false;
+#pragma unroll
+  for (int h = 0; h < 8; ++h) {
+    const int cx = h & 1, cy = (h >> 1) & 1, cz = h >> 2;
+    const double wx[3] = {cx ? -0.125 : 0.125, 1.0, cx ? 0.125 : -0.125};
+    const double wy[3] = {cy ? -0.125 : 0.125, 1.0, cy ? 0.125 : -0.125};
+    const double wz[3] = {cz ? -0.125 : 0.125, 1.0, cz ? 0.125 : -0.125};
+    double sum = 0.0;
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+      for (int p2 = 0; p2 < 3; ++p2)
+#pragma unroll
+        for (int p1 = 0; p1 < 3; ++p1) sum += wx[p1] * wy[p2] * wz[r] * u[p1 + 3 * p2 + 9 * r];
+    ch[h] = sum;
+    fall = fall || sum < mn || sum > mx;
+  }
+  if (fall) {
+    const double uc = u[13];
+    const double sx = mm(u[14] - uc, uc - u[12]), sy = mm(u[16] - uc, uc - u[10]), sz = mm(u[22] - uc, uc - u[4]);
+#pragma unroll
+    for (int h = 0; h < 8; ++h)
+      ch[h] = uc + ((h & 1) ? 0.25 : -0.25) * sx + (((h >> 1) & 1) ? 0.25 : -0.25) * sy + ((h >> 2) ? 0.25 : -0.25) * sz;
+  }
+  double* o = a.dst + (size_t)q * Nf;
+#pragma unroll
+  for (int h = 0; h < 8; h += 2)
+    store_children(a, o, 2 * (cc[0] - a.c0[0]), 2 * (cc[1] - a.c0[1]) + ((h >> 1) & 1), 2 * (cc[2] - a.c0[2]) + (h >> 2),
+                   ch[h], ch[h + 1]);
 }
 
 DEV void restrict_body(const InterArgs& a, unsigned tile) {
@@ -2430,8 +2459,12 @@ __global__ __launch_bounds__(256) void k_tmunu(GD g, TmunuArgs ta) {
   __shared__ TmunuLDS L;
   tmunu_body(g, ta, my_tile(), L);
 }
-__global__ __launch_bounds__(256) void k_prolong(InterArgs a) { prolong_body(a, my_tile()); }
-__global__ __launch_bounds__(256) void k_prolong_cells(InterArgs a) { prolong_cells_body(a, my_tile()); }
+template <int STAG>
+__global__ __launch_bounds__(256) void k_prolong(InterArgs a) { prolong_body<STAG>(a, my_tile()); }
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_prolong_cells(InterArgs a) {
+  const unsigned per = gridDim.x / (unsigned)a.nf;
+  prolong_cells_body(a, xcd_block(blockIdx.x % per, per), (int)(blockIdx.x / per));
+}
 __global__ __launch_bounds__(256) void k_restrict(InterArgs a) { restrict_body(a, my_tile()); }
 __global__ __launch_bounds__(256) void kb_vertex(const PatchDesc* __restrict__ P, const Item* __restrict__ it, int nit,
                                                  VertexArgs va) {
@@ -4120,18 +4153,20 @@ int inter_launch(const asterx_grid* gc, const asterx_grid* gf, const int32_t* c0
   a.src = src;
   a.dst = dst;
   int e[3] = {hi[0] - lo[0] + 1, hi[1] - lo[1] + 1, hi[2] - lo[2] + 1};
-  const bool cells = !stag[0] && !stag[1] && !stag[2];
-  if (prolong && cells)
+  if (prolong)
     for (int d = 0; d < 3; ++d) {
       auto fd = [](int f) { return f >= 0 ? f / 2 : -((1 - f) / 2); };
       e[d] = fd(hi[d]) - fd(lo[d]) + 1;  // coarse parents of the fine box
     }
   hipStream_t s = (hipStream_t)stream;
-  return timed(KT_INTER, s, [&] {
-    if (prolong && cells) hipLaunchKernelGGL(k_prolong_cells, dim3(lin_blocks(e)), dim3(256), 0, s, a);
-    else if (prolong) hipLaunchKernelGGL(k_prolong, dim3(lin_blocks(e)), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL(k_restrict, dim3(lin_blocks(e)), dim3(256), 0, s, a);
-  });
+  void (*kern)(InterArgs) = k_restrict;
+  if (prolong) {
+    void (*const by_stag[8])(InterArgs) = {k_prolong_cells, k_prolong<1>, k_prolong<2>, k_prolong<3>,
+                                           k_prolong<4>,    k_prolong<5>, k_prolong<6>, k_prolong<7>};
+    kern = by_stag[stag[0] + 2 * stag[1] + 4 * stag[2]];
+  }
+  const unsigned nb = lin_blocks(e) * (kern == k_prolong_cells ? (unsigned)nf : 1u);
+  return timed(KT_INTER, s, [&] { hipLaunchKernelGGL(kern, dim3(nb), dim3(256), 0, s, a); });
 }
 
 int asterx_prolong(const asterx_grid* coarse, const asterx_grid* fine, const int32_t* c0, const int32_t* stag,
