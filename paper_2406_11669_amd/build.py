@@ -15,9 +15,6 @@ CODEGEN_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
     # packed FP32 instructions are kept out of every kernel
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    # the scheduler's instruction-level-parallelism strategy: the latency-bound face and recovery kernels
-    # issue their loads and FP64 chains further apart (the same arithmetic, 1.2% more zone-updates/s)
-    "-mllvm", "-amdgpu-sched-strategy=max-ilp",
 ]
 FLAGS = CODEGEN_FLAGS + ["-I", os.path.join(ROOT, "include"), "-I", os.path.join(HERE, "csrc")]
 
