@@ -4403,13 +4403,17 @@ int check_adjoint(const asterx_grid* gr, const asterx_params* p, size_t ws_bytes
   return 0;
 }
 
-// Zero the workspace, copy the stage input, recompute c2p (flags in the workspace tail) and the
-// centre field.
+// Zero workspace fields [AW_PBAR, zero_end), copy the stage input, recompute c2p (flags in the workspace tail) and
+// the centre field.  The fields before are written here; the flux cotangents and, in a stage's adjoint, those that
+// the left faces' cotangents take first, are written before they are read (64^3: clearing all 52 took 17 us a call).
 int adj_prologue(const GD& g, const asterx_params* p, const double* metric, const double* cons,
-                 const double* prim_guess, const double* A, double* ws, uint8_t* flags, hipStream_t s, bool with_c2p) {
+                 const double* prim_guess, const double* A, double* ws, uint8_t* flags, hipStream_t s, bool with_c2p,
+                 int zero_end) {
   int rc;
-  long long nzero = (long long)AW_FIELDS * (long long)g.N;
-  if ((rc = timed(KT_ZERO, s, [&] { hipLaunchKernelGGL(k_zero, dim3(pts_blocks(nzero)), dim3(256), 0, s, ws, nzero); })))
+  long long nzero = (long long)(zero_end - AW_PBAR) * (long long)g.N;
+  if ((rc = timed(KT_ZERO, s, [&] {
+         hipLaunchKernelGGL(k_zero, dim3(pts_blocks(nzero)), dim3(256), 0, s, ws + AW_PBAR * g.N, nzero);
+       })))
     return rc;
   if ((rc = do_bcent(g, A, ws + AW_BC * g.N, s))) return rc;
   if (!with_c2p) return 0;
@@ -4452,14 +4456,14 @@ int adj_epilogue(const GD& g, double* ws, double* A_bar, double* psi_bar, hipStr
          hipLaunchKernelGGL(k_curlT, dim3(nb), dim3(256), 0, s, g, ws + AW_BFBAR * g.N, ws + AW_ABAR * g.N);
        })))
     return rc;
-  if ((rc = adj_fillT(g, ws + AW_ABAR * g.N, 3, s))) return rc;
+  // Psi's cotangent is the field after the potential's three
+  if ((rc = adj_fillT(g, ws + AW_ABAR * g.N, psi_bar ? 4 : 3, s))) return rc;
   unsigned no = tiles_for(PH_RK, g);
   if (A_bar) {
     AccumArgs aa{ws + AW_ABAR * g.N, A_bar, 3};
     if ((rc = timed(KT_ADJ, s, [&] { hipLaunchKernelGGL(k_accum, dim3(no), dim3(256), 0, s, g, aa); }))) return rc;
   }
   if (psi_bar) {
-    if ((rc = adj_fillT(g, ws + AW_PSIBAR * g.N, 1, s))) return rc;
     AccumArgs pa{ws + AW_PSIBAR * g.N, psi_bar, 1};
     if ((rc = timed(KT_ADJ, s, [&] { hipLaunchKernelGGL(k_accum, dim3(no), dim3(256), 0, s, g, pa); }))) return rc;
   }
@@ -4492,7 +4496,7 @@ int asterx_rhs_adjoint(const asterx_grid* gr, const asterx_params* p, const doub
   double* ws = (double*)workspace;
   uint8_t* flags = (uint8_t*)(ws + (size_t)AW_FIELDS * g.N);
   double* slots = gamma_slots(g, ws);
-  if ((rc = adj_prologue(g, p, metric, cons, prim_guess, A, ws, flags, s, true))) return rc;
+  if ((rc = adj_prologue(g, p, metric, cons, prim_guess, A, ws, flags, s, true, AW_XBAR))) return rc;
   if ((rc = gslots_zero(slots, s))) return rc;
   unsigned nb;
   // fluxbar and vertex_adj tile the (n + 2)^3 vertex box 64 x 4
@@ -4551,7 +4555,7 @@ int asterx_c2p_adjoint(const asterx_grid* gr, const asterx_params* p, const doub
   double* ws = (double*)workspace;
   uint8_t* flags = (uint8_t*)(ws + (size_t)AW_FIELDS * g.N);
   double* slots = gamma_slots(g, ws);
-  if ((rc = adj_prologue(g, p, metric, cons, prim_guess, A, ws, flags, s, true))) return rc;
+  if ((rc = adj_prologue(g, p, metric, cons, prim_guess, A, ws, flags, s, true, AW_PSIBAR))) return rc;
   if ((rc = gslots_zero(slots, s))) return rc;
   unsigned no = tiles_for(PH_RK, g);
   AccumArgs cp{prim_bar, ws + AW_PBAR * g.N, 5};
@@ -4577,7 +4581,7 @@ int asterx_prim2con_adjoint(const asterx_grid* gr, const asterx_params* p, const
   GD g = make_gd(gr);
   double* ws = (double*)workspace;
   double* slots = gamma_slots(g, ws);
-  if ((rc = adj_prologue(g, p, metric, nullptr, nullptr, A, ws, nullptr, s, false))) return rc;
+  if ((rc = adj_prologue(g, p, metric, nullptr, nullptr, A, ws, nullptr, s, false, AW_PSIBAR))) return rc;
   if ((rc = gslots_zero(slots, s))) return rc;
   unsigned no = tiles_for(PH_RK, g);
   AccumArgs cp{cons_bar, ws + AW_PBAR * g.N, 5};
