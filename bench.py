@@ -45,14 +45,13 @@ FACE_FLOPS = {"ppm": 2603.1, "wenoz": 3955.0, "minmod": 2022.6, "mp5": 2480.3, "
 # Noble iteration) on that block.
 CELL_FLOPS = 4716.0
 C2P_FLOPS = 1795.0
-# The benchmark's stage evaluates the sources in the recovery kernel (asterx_c2p_src) and leaves the flux
-# divergence, div B and the stage outputs to a streaming kernel (asterx_rhs_rk_src).  Counted per cell: the
-# divergence 5 components x (3 differences, 3 divisions by the spacing, 3 additions, 1 source addition) = 50, and
-# div B 6 face curls x 5 (the counter's face_B) + 3 differences + 3 divisions + 2 additions = 38; the recovery
-# with sources is the recovery plus the cell count without these, less the ten centre metric values the two
-# counts both contain (10 x 147, the counter's centre_value), which the fused kernel interpolates once.
+# The benchmark's stage evaluates the sources in the recovery kernel, from spacetime data interpolated once per step
+# (asterx_geometry, asterx_c2p_geo), and leaves the flux divergence, div B and the stage outputs to a streaming
+# kernel (asterx_rhs_rk_geo).  Counted per cell: the divergence 5 components x (3 differences, 3 divisions by the
+# spacing, 3 additions, 1 source addition) = 50, and div B 6 face curls x 5 (the counter's face_B) + 3 differences +
+# 3 divisions + 2 additions = 38.  The counts above contain the interpolation, which the stored data leaves out of
+# the stages (10 values per face; per cell 10 values, 30 derivatives, 6 curvature values): no count for the recovery.
 DIV_FLOPS = 50.0 + 38.0
-C2P_SRC_FLOPS = C2P_FLOPS + CELL_FLOPS - DIV_FLOPS - 10 * 147.0
 # Algorithmic bytes per face: read 5 primitives + 2 centre fields + 10 face-metric components + 2 potential
 # components, write 7 face fluxes (each value once, stencil reuse served on chip).
 FACE_BYTES = 8.0 * (5 + 2 + 10 + 2 + 7)
@@ -63,9 +62,9 @@ CELL_BYTES_RK4 = 8.0 * (16 + 5 + 3 + 15 + 1.5 * 5 + 1.75 * 5)
 # Per owned cell of the recovery: conserved (5), potential (3), metric (10), previous primitives (5) read,
 # primitives (5) written.
 C2P_BYTES = 8.0 * (5 + 3 + 10 + 5 + 5)
-# Per owned cell of the recovery with sources: the recovery's and the curvature (6) read; the primitives (5), the
-# densitized sources (4) and the metric at the cell's lower x face (10, handed to the x-face kernel) written.
-C2P_SRC_BYTES = 8.0 * (5 + 3 + 10 + 6 + 5 + 5 + 4 + 10)
+# Per owned cell of the recovery with sources: conserved (5), potential (3), previous primitives (5), the stored
+# centre metric, its derivatives and the curvature (46) read; the primitives (5) and the densitized sources (4) written.
+C2P_GEO_BYTES = 8.0 * (5 + 3 + 5 + 46 + 5 + 4)
 # Per owned cell of the divergence kernel: the 15 hydro face fluxes, the 4 sources and the potential (3, for
 # div B) read once; RK4 stage outputs of the 5 hydro fields as for the cell kernel.
 DIV_BYTES_RK4 = 8.0 * (15 + 4 + 3 + 1.5 * 5 + 1.75 * 5)
@@ -318,8 +317,8 @@ def kernel_rooflines(kt, stages, n, scheme, ct):
         "face": dict(ms=face_ms, launches_per_stage=3, units="faces", units_per_launch=faces,
                      flops={"estimate": SURVEY_FLOPS_PER_FACE, "oracle_count": FACE_FLOPS.get(scheme)},
                      bytes=FACE_BYTES),
-        "c2p_src": dict(ms=kt["c2p"][0] / max(1, kt["c2p"][1]), launches_per_stage=1, units="cells",
-                        units_per_launch=cells, flops={"oracle_count": C2P_SRC_FLOPS}, bytes=C2P_SRC_BYTES),
+        "c2p_geo": dict(ms=kt["c2p"][0] / max(1, kt["c2p"][1]), launches_per_stage=1, units="cells",
+                        units_per_launch=cells, flops={}, bytes=C2P_GEO_BYTES),
         "divergence": dict(ms=kt["cell"][0] / max(1, kt["cell"][1]), launches_per_stage=1, units="cells",
                            units_per_launch=cells, flops={"oracle_count": DIV_FLOPS}, bytes=DIV_BYTES_RK4),
     }
@@ -345,7 +344,7 @@ def headline_roofline(kr, kt, stages, scheme, n):
     kernel's three direction launches are one kernel).  Its bound follows from the arithmetic intensity of the
     a-priori per-unit figures (FLOP/B against the ridge of the two roofs)."""
     per_stage = {"face": kr["face"]["ms_per_launch"] * 3, "divergence": kr["divergence"]["ms_per_launch"],
-                 "c2p_src": kr["c2p_src"]["ms_per_launch"]}
+                 "c2p_geo": kr["c2p_geo"]["ms_per_launch"]}
     for k, v in kt.items():
         if k not in ("face_x", "face_y", "face_z", "cell", "c2p") and v[1] > 0:
             per_stage[k] = v[0] / stages
@@ -355,7 +354,7 @@ def headline_roofline(kr, kt, stages, scheme, n):
     if dom not in kr:
         dom = "face"
     est = e["flops_per_unit"].get("estimate") or e["flops_per_unit"].get("oracle_count")
-    intensity = est / e["bytes_per_unit"]
+    intensity = (est or 0.0) / e["bytes_per_unit"]
     bound = "hbm" if intensity < RIDGE else "alu"
     if bound == "hbm":
         achieved, peak, unit = e["algorithmic_GBs"], HBM_PEAK_GBS, "GB/s"
@@ -562,7 +561,7 @@ def main():
     kt = asterx.timing_read()
     asterx.timing_enable(False)
     # the library times the recovery with sources as "c2p" and the divergence kernel as "cell"
-    names = {"c2p": "c2p_src", "cell": "divergence"}
+    names = {"c2p": "c2p_geo", "cell": "divergence"}
     per_stage = {names.get(k, k): round(v[0] / stages, 4) for k, v in kt.items() if v[1] > 0}
     kr = kernel_rooflines(kt, stages, n, scheme, args.ct)
     roofline = headline_roofline(kr, kt, stages, scheme, n)
