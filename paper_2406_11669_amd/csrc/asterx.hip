@@ -1562,13 +1562,13 @@ __host__ __device__ inline unsigned face_items(const int n[3], int D, int lo, in
   return (unsigned)((cols + 63) / 64 * ((n[D] + rows) / rows));
 }
 // Faces per march.  A march of r faces costs r + 1 reconstructions and r solutions (which cost about the same),
-// and its five-row windows have to stay in L2 with those of all marches in flight: at 128^3 with PPM the y + z
-// faces took 0.417 ms in marches of 1, 0.367 of 2, 0.380 of 3, 0.403 of 4, 0.456 of 16, with WENO-Z 0.446 of 2,
-// 0.420 of 3, 0.445 of 4: at most two, WENO-Z three.  Blocks whose marches fill the chip's wavefront slots only a
-// few times take the length whose rounds cost least (48^3, PPM: y faces 20 us in marches of 1, 24 of 2; 96^3: 95
-// and 87 us).
+// and its five-row windows have to stay in L2 with those of all marches in flight: at most three, MINMOD, whose
+// reconstruction is the shortest, two (RK4 steps, marches of at most 1, 2, 3, 4: 128^3, PPM, 5.21, 5.02, 4.98,
+// 5.03 ms; 96^3, WENO-Z, 2.50, 2.39, 2.38, 2.38; 80^3, MINMOD, 1.281, 1.284, 1.295, 1.297).  Blocks whose marches
+// fill the chip's wavefront slots only a few times take the length whose rounds cost least (97 x 61 x 45, MP5,
+// upwind CT: single faces 1.112 ms, by the rule 1.058).
 template <int R>
-constexpr int face_march() { return R == ASTERX_RECON_WENOZ ? 3 : 2; }
+constexpr int face_march() { return R == ASTERX_RECON_MINMOD ? 2 : 3; }
 constexpr int FACE_BATCH_ROWS = 2;
 constexpr unsigned FACE_SLOTS = 256 * 4 * 3;  // 256 CUs of four SIMDs, three wavefronts each
 inline int face_rows(const int n[3], int D, int lo, int march) {
