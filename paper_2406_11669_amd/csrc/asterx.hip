@@ -115,7 +115,8 @@ DEV bool lin_at(const int e[3], unsigned tile, unsigned tid, int& a, int& b, int
 }
 inline unsigned lin_blocks(const int e[3]) { return (unsigned)(((long long)e[0] * e[1] * e[2] + 255) / 256); }
 
-// Face tiles.  Face grids are n + 1 wide (129 for n = 128), so 32-wide tile rows would leave
+// Face tiles of the adjoint (two lanes per face; the figures were measured when the forward kernels had this
+// form).  Face grids are n + 1 wide (129 for n = 128), so 32-wide tile rows would leave
 // up to 31 of every 160 lanes idle.  In each z plane, the x range rounded down to a multiple
 // of 32 is tiled 32 x 4 (x, y); the remaining x columns (fewer than 32) follow in the same
 // plane, 128 faces per tile, x fastest.  Keeping them beside their plane's main tiles spreads

@@ -132,3 +132,28 @@ def test_stage_variants_agree(ax, n, recon, ct):
     for kind in ("src", "geo"):
         assert_fields_close(outs[kind][0], outs["plain"][0], 1e-13, L.owned, STATE_NAMES)
         assert_fields_close(outs[kind][1], outs["plain"][1], 1e-13, L.owned, PRIM_NAMES)
+
+
+def test_block_without_room_for_the_geometry(ax, monkeypatch):
+    """A block whose stored geometry cannot be allocated takes the recovery with sources: the same steps within 1e-13."""
+    import torch
+    w = W.curved_block(seed=64, n=(18, 9, 7), recon="ppm", nsteps=2, rk=4)
+    print("case block without stored geometry", flush=True)
+    ref = ax.Block(w)
+    real = torch.empty
+
+    def empty(*a, **k):
+        if a and isinstance(a[0], tuple) and a[0][0] == ax.GEO_FIELDS:
+            raise torch.OutOfMemoryError("no room")
+        return real(*a, **k)
+
+    monkeypatch.setattr(torch, "empty", empty)
+    blk = ax.Block(w)
+    monkeypatch.undo()
+    assert blk.geo is None and ref.geo is not None
+    for b in (ref, blk):
+        b.run(2)
+    torch.cuda.synchronize()
+    assert torch.equal(blk.stats, ref.stats)
+    assert_fields_close(blk.state.cpu().numpy(), ref.state.cpu().numpy(), 1e-13, w.layout.owned, STATE_NAMES)
+    assert_fields_close(blk.prim.cpu().numpy(), ref.prim.cpu().numpy(), 1e-13, w.layout.owned, PRIM_NAMES)
