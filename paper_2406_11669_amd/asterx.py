@@ -739,6 +739,8 @@ class Batch:
         self._call("asterx_batch_fill_ghosts", _ptr(f), f.shape[0], _kinds(kinds), _stream(None))
 
     def fill_state(self, U):
+        if U.shape[0] < 9:
+            raise ValueError("fill_state: a state has nine fields")
         self._call("asterx_batch_fill_state", _ptr(U), _kinds(self.bc_cell), _kinds(self.bc_A), _stream(None))
 
     def rk(self, a, us, b_dt, rhs_t, out):
