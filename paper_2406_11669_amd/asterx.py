@@ -258,14 +258,17 @@ def _kinds(kinds):
 
 
 def fill_state(layout, u, kinds_cell, kinds_A, A_shift=None, stream=None):
-    """Ghosts of a nine-field state in one launch: A by kinds_A or, with A_shift, as fill_ghosts_shift fills it."""
-    sh = None
+    """Ghosts of a nine-field state in one launch: A by kinds_A or, with A_shift, as fill_ghosts_shift fills it
+    (kinds_A is then unused and may be None)."""
+    sh = kA = None
     if A_shift is not None:
         sh = (ctypes.c_double * 9)(*np.asarray(A_shift, dtype=np.float64)[:3].ravel().tolist())
+    else:
+        kA = _kinds(kinds_A)
     if u.shape[0] != 9:
         raise ValueError("fill_state: a state has nine fields")
-    _check(lib().asterx_fill_state(ctypes.byref(make_grid(layout)), _ptr(_f64(u)), _kinds(kinds_cell),
-                                   _kinds(kinds_A), sh, _stream(stream)))
+    _check(lib().asterx_fill_state(ctypes.byref(make_grid(layout)), _ptr(_f64(u)), _kinds(kinds_cell), kA, sh,
+                                   _stream(stream)))
 
 
 def fill_ghosts(layout, f, kinds, stream=None):
