@@ -561,6 +561,11 @@ class Block:
         """Switch to the metric of time t when the spacetime is time dependent."""
         if self.metric_fn is not None:
             self.metric, self.curv = self.metric_fn(t)
+
+    def _at_time(self, t):
+        self.at_time(t)
+        # a metric_fn or a subclass's at_time may have changed the metric, also in place
+        if self.metric_fn is not None or getattr(self.at_time, "__func__", None) is not Block.at_time:
             self._geo_held = False
 
     def recover(self, U):
@@ -614,23 +619,23 @@ class Block:
         U0 = self.state
         if self.wl.rk == 2:
             U1 = self.tmp
-            self.at_time(t)
+            self._at_time(t)
             self.stage(U0, [([1.0], [U0], dt, U1)])
             self.fill_state(U1)
-            self.at_time(t + dt)
+            self._at_time(t + dt)
             self.stage(U1, [([0.5, 0.5], [U0, U1], 0.5 * dt, U0)])
             self.fill_state(U0)
         else:
             Ua, Ub, acc = self.tmp, self.tmp2, self.acc
-            self.at_time(t)
+            self._at_time(t)
             self.stage(U0, [([1.0], [U0], dt / 6.0, acc), ([1.0], [U0], 0.5 * dt, Ua)])
             self.fill_state(Ua)
-            self.at_time(t + 0.5 * dt)
+            self._at_time(t + 0.5 * dt)
             self.stage(Ua, [([1.0], [acc], dt / 3.0, acc), ([1.0], [U0], 0.5 * dt, Ub)])
             self.fill_state(Ub)
             self.stage(Ub, [([1.0], [acc], dt / 3.0, acc), ([1.0], [U0], dt, Ua)])
             self.fill_state(Ua)
-            self.at_time(t + dt)
+            self._at_time(t + dt)
             self.stage(Ua, [([1.0], [acc], dt / 6.0, U0)])
             self.fill_state(U0)
 
@@ -639,22 +644,22 @@ class Block:
         U0, K = self.state, self.k
         if self.wl.rk == 2:
             U1 = self.tmp
-            self.at_time(t)
+            self._at_time(t)
             self.eval_rhs(U0, K)
             rk_stage(self.L, [1.0], [U0], dt, K, U1)
             self.fill_state(U1)
-            self.at_time(t + dt)
+            self._at_time(t + dt)
             self.eval_rhs(U1, K)
             rk_stage(self.L, [0.5, 0.5], [U0, U1], 0.5 * dt, K, U0)
             self.fill_state(U0)
         else:
             Ut, acc = self.tmp, self.acc
-            self.at_time(t)
+            self._at_time(t)
             self.eval_rhs(U0, K)
             rk_stage(self.L, [1.0], [U0], 0.5 * dt, K, Ut)
             rk_stage(self.L, [1.0], [U0], dt / 6.0, K, acc)
             self.fill_state(Ut)
-            self.at_time(t + 0.5 * dt)
+            self._at_time(t + 0.5 * dt)
             self.eval_rhs(Ut, K)
             rk_stage(self.L, [1.0], [acc], dt / 3.0, K, acc)
             rk_stage(self.L, [1.0], [U0], 0.5 * dt, K, Ut)
@@ -663,7 +668,7 @@ class Block:
             rk_stage(self.L, [1.0], [acc], dt / 3.0, K, acc)
             rk_stage(self.L, [1.0], [U0], dt, K, Ut)
             self.fill_state(Ut)
-            self.at_time(t + dt)
+            self._at_time(t + dt)
             self.eval_rhs(Ut, K)
             rk_stage(self.L, [1.0], [acc], dt / 6.0, K, U0)
             self.fill_state(U0)

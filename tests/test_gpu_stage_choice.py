@@ -1,0 +1,46 @@
+"""GPU: which form a block's stages take (stored geometry or not), and that every form sees the metric of its stage."""
+import numpy as np
+import pytest
+
+from paper_2406_11669_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ax():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2406_11669_amd import asterx
+    asterx.lib()
+    return asterx
+
+
+def _lapse(w, t):
+    """The workload's metric with the lapse and the shift scaled by a function of time."""
+    f = 1.0 + 0.1 * np.sin(2.0 * np.pi * t / (3.0 * w.dt))
+    m = w.metric.copy()
+    m[0] *= f
+    m[1:4] *= 2.0 - f
+    return m
+
+
+@pytest.mark.parametrize("rk", [2, 4])
+def test_at_time_overridden_in_place(ax, rk):
+    """A subclass that advances the metric in place in at_time: bit for bit the steps of a metric_fn that returns
+    the same data (no stage may read data interpolated from another stage's metric)."""
+    import torch
+    w = W.curved_block(seed=71, n=(18, 9, 7), recon="ppm", nsteps=2, rk=rk)
+    print("case at_time in place", rk, flush=True)
+
+    class Driven(ax.Block):
+        def at_time(self, t):
+            self.metric.copy_(torch.from_numpy(_lapse(w, t)))
+
+    a = Driven(w)
+    b = ax.Block(w, metric_fn=lambda t: (torch.from_numpy(_lapse(w, t)).cuda(), a.curv))
+    for blk in (a, b):
+        blk.run(2)
+    torch.cuda.synchronize()
+    assert torch.equal(a.state, b.state) and torch.equal(a.prim, b.prim) and torch.equal(a.red, b.red)
