@@ -52,6 +52,9 @@ C2P_FLOPS = 1795.0
 # 3 divisions + 2 additions = 38.  The counts above contain the interpolation, which the stored data leaves out of
 # the stages (10 values per face; per cell 10 values, 30 derivatives, 6 curvature values): no count for the recovery.
 DIV_FLOPS = 50.0 + 38.0
+# The edge kernel shares the divergence's launch.  Counted per cell (flux CT, Lorenz gauge): three edge averages of
+# four fluxes 12, three gradients of the gauge quantity 9, its divergence 8, the damping term 3.
+EDGE_FLOPS = 32.0
 # Algorithmic bytes per face: read 5 primitives + 2 centre fields + 10 face-metric components + 2 potential
 # components, write 7 face fluxes (each value once, stencil reuse served on chip).
 FACE_BYTES = 8.0 * (5 + 2 + 10 + 2 + 7)
@@ -68,6 +71,9 @@ C2P_GEO_BYTES = 8.0 * (5 + 3 + 5 + 46 + 5 + 4)
 # Per owned cell of the divergence kernel: the 15 hydro face fluxes, the 4 sources and the potential (3, for
 # div B) read once; RK4 stage outputs of the 5 hydro fields as for the cell kernel.
 DIV_BYTES_RK4 = 8.0 * (15 + 4 + 3 + 1.5 * 5 + 1.75 * 5)
+# Per owned cell of the edge kernel: the 6 induction fluxes, the 4 gauge quantities, lapse and Psi read once; RK4
+# stage outputs of the potential and Psi.
+EDGE_BYTES_RK4 = 8.0 * (6 + 4 + 2 + 1.5 * 4 + 1.75 * 4)
 # Whole-stage algorithmic HBM bytes per zone-stage, RK4 averaged over its four stages: reads of the stage
 # state (9), metric and curvature (16), previous primitives (5), RK base state and accumulator (9 + 9 when
 # used); writes of primitives (5), next state (9) and accumulator (9 when used).
@@ -104,7 +110,7 @@ def measured_face_traffic(recon, n):
     value, sha = None, None
     with open(path) as f:
         for line in f:
-            if line.startswith("face kernel, average of the three directions: traffic bytes per launch:"):
+            if line.startswith("face kernel, the three directions in one launch: traffic bytes per launch:"):
                 value = float(line.rsplit(":", 1)[1])
             elif line.startswith("library source sha256"):
                 sha = line.rsplit(":", 1)[1].strip()
@@ -305,22 +311,23 @@ def graph_steps(torch, blk, steps, warmup, graph=True):
 
 
 def kernel_rooflines(kt, stages, n, scheme, ct):
-    """Per-kernel figures from the live HIP-event durations kt (one eager step): the face kernel (three direction
-    launches per stage, averaged), the recovery with sources (timed under "c2p") and the divergence kernel (timed
-    under "cell"), each against both roofs.  Achieved figures are algorithmic work per launch (per-unit figure x
-    units per launch) over the average launch duration."""
+    """Per-kernel figures from the live HIP-event durations kt (one eager step): the face kernel (the three directions
+    in one launch per stage), the recovery with sources (timed under "c2p") and the divergence with the edge field
+    (one launch), each against both roofs.  Achieved figures are algorithmic work per launch (per-unit figure x units
+    per launch) over the average launch duration."""
     cells = n ** 3
     faces = (n + 1) ** 3 if ct == "fct" else (n + 1) * (n + 5) ** 2
-    face_keys = ("face_x", "face_y", "face_z")
-    face_ms = sum(kt[k][0] for k in face_keys) / max(1, sum(kt[k][1] for k in face_keys))
+    avg = lambda k: kt[k][0] / max(1, kt[k][1])
     rows = {
-        "face": dict(ms=face_ms, launches_per_stage=3, units="faces", units_per_launch=faces,
-                     flops={"estimate": SURVEY_FLOPS_PER_FACE, "oracle_count": FACE_FLOPS.get(scheme)},
-                     bytes=FACE_BYTES),
-        "c2p_geo": dict(ms=kt["c2p"][0] / max(1, kt["c2p"][1]), launches_per_stage=1, units="cells",
-                        units_per_launch=cells, flops={}, bytes=C2P_GEO_BYTES),
-        "divergence": dict(ms=kt["cell"][0] / max(1, kt["cell"][1]), launches_per_stage=1, units="cells",
-                           units_per_launch=cells, flops={"oracle_count": DIV_FLOPS}, bytes=DIV_BYTES_RK4),
+        "faces": dict(ms=avg("faces"), launches_per_stage=1, units="faces", units_per_launch=3 * faces,
+                      flops={"estimate": SURVEY_FLOPS_PER_FACE, "oracle_count": FACE_FLOPS.get(scheme)},
+                      bytes=FACE_BYTES),
+        "c2p_geo": dict(ms=avg("c2p"), launches_per_stage=1, units="cells", units_per_launch=cells, flops={},
+                        bytes=C2P_GEO_BYTES),
+        "divergence+edge": dict(ms=avg("divergence+edge"), launches_per_stage=1, units="cells",
+                                units_per_launch=cells,
+                                flops={"oracle_count": DIV_FLOPS + EDGE_FLOPS} if ct == "fct" else {},
+                                bytes=DIV_BYTES_RK4 + EDGE_BYTES_RK4),
     }
     out = {}
     for name, r in rows.items():
@@ -340,19 +347,18 @@ def kernel_rooflines(kt, stages, n, scheme, ct):
 
 
 def headline_roofline(kr, kt, stages, scheme, n):
-    """The roofline of the dominant kernel: the kernel function with the largest total time per stage (the face
-    kernel's three direction launches are one kernel).  Its bound follows from the arithmetic intensity of the
-    a-priori per-unit figures (FLOP/B against the ridge of the two roofs)."""
-    per_stage = {"face": kr["face"]["ms_per_launch"] * 3, "divergence": kr["divergence"]["ms_per_launch"],
-                 "c2p_geo": kr["c2p_geo"]["ms_per_launch"]}
+    """The roofline of the dominant kernel: the kernel function with the largest total time per stage.  Its bound
+    follows from the arithmetic intensity of the a-priori per-unit figures (FLOP/B against the ridge of the two
+    roofs)."""
+    per_stage = {k: kr[k]["ms_per_launch"] for k in kr}
     for k, v in kt.items():
-        if k not in ("face_x", "face_y", "face_z", "cell", "c2p") and v[1] > 0:
+        if k not in ("faces", "divergence+edge", "c2p") and v[1] > 0:
             per_stage[k] = v[0] / stages
     dom = max(per_stage, key=per_stage.get)
     largest_launch = max(((k, v[0] / max(1, v[1])) for k, v in kt.items() if v[1] > 0), key=lambda kv: kv[1])[0]
-    e = kr.get(dom, kr["face"])
+    e = kr.get(dom, kr["faces"])
     if dom not in kr:
-        dom = "face"
+        dom = "faces"
     est = e["flops_per_unit"].get("estimate") or e["flops_per_unit"].get("oracle_count")
     intensity = (est or 0.0) / e["bytes_per_unit"]
     bound = "hbm" if intensity < RIDGE else "alu"
@@ -361,12 +367,12 @@ def headline_roofline(kr, kt, stages, scheme, n):
     else:
         achieved = est * e["units_per_launch"] / (e["ms_per_launch"] * 1e-3) / 1e12
         peak, unit = FP64_VECTOR_PEAK_TFLOPS, "TFLOP/s"
-    return {"kernel": dom + (" (x, y, z launches averaged)" if dom == "face" else ""),
+    return {"kernel": dom + (" (x, y, z in one launch)" if dom == "faces" else ""),
             "dominant_by": "kernel time per stage (%s)" % ", ".join("%s %.3f ms" % kv for kv in sorted(
                 per_stage.items(), key=lambda kv: -kv[1])[:4]),
             "largest_single_launch": largest_launch, "bound": bound, "achieved": round(achieved, 3), "peak": peak,
             "unit": unit, "frac": round(achieved / peak, 4),
-            "traffic": measured_face_traffic(scheme, n) if dom == "face" else None,
+            "traffic": measured_face_traffic(scheme, n) if dom == "faces" else None,
             "avg_launch_ms": e["ms_per_launch"], "units_per_launch": e["units_per_launch"],
             "flops_per_unit": e["flops_per_unit"], "bytes_per_unit": e["bytes_per_unit"],
             "intensity_flop_per_byte": round(intensity, 2), "ridge_flop_per_byte": round(RIDGE, 2),
@@ -560,8 +566,8 @@ def main():
     torch.cuda.synchronize()
     kt = asterx.timing_read()
     asterx.timing_enable(False)
-    # the library times the recovery with sources as "c2p" and the divergence kernel as "cell"
-    names = {"c2p": "c2p_geo", "cell": "divergence"}
+    # the library times the recovery with sources as "c2p"
+    names = {"c2p": "c2p_geo"}
     per_stage = {names.get(k, k): round(v[0] / stages, 4) for k, v in kt.items() if v[1] > 0}
     kr = kernel_rooflines(kt, stages, n, scheme, args.ct)
     roofline = headline_roofline(kr, kt, stages, scheme, n)

@@ -2480,8 +2480,9 @@ __global__ __launch_bounds__(256) void kb_vertex(const PatchDesc* __restrict__ P
 __global__ __launch_bounds__(256) void k_edge(GD g, EdgeArgs ea) { edge_body(g, ea, my_tile()); }
 __global__ __launch_bounds__(256) void k_edge_uct(GD g, EdgeArgs ea) { edge_body<true>(g, ea, my_tile()); }
 // Two phases that don't depend on each other in one launch, the first n0 workgroups for the first: the centre
-// field and the gauge quantities before the faces, the divergence and the edges after them.  Small blocks save the
-// launches (16^3 and 32^3: about 3 us each from a graph, 5 eagerly).
+// field and the gauge quantities before the faces, the divergence and the edges after them.  RK4 steps from a graph,
+// PPM, the first pair apart, the second pair apart, both in one launch: 16^3 0.163, 0.173, 0.154 ms; 64^3 0.722, 0.725,
+// 0.709; 128^3 4.959, 4.944, 4.925; 192^3 15.80, 15.80, 15.78.
 __global__ __launch_bounds__(256) void k_bcent_vertex(GD g, const double* A, double* bc, VertexArgs va, unsigned n0) {
   if (blockIdx.x < n0) bcent_body(g, A, bc, xcd_block(blockIdx.x, n0));
   else vertex_body(g, va, xcd_block(blockIdx.x - n0, gridDim.x - n0));
@@ -3351,11 +3352,11 @@ int launched() {
 // use while a stream is being captured into a graph.
 enum {
   KT_PRIM2CON, KT_C2P, KT_FILL, KT_BCENT, KT_FACE_X, KT_FACE_Y, KT_FACE_Z, KT_CELL, KT_VERTEX, KT_EDGE, KT_RK,
-  KT_ZERO, KT_ADJ, KT_TMUNU, KT_INTER, KT_GEOM, KT_N
+  KT_ZERO, KT_ADJ, KT_TMUNU, KT_INTER, KT_GEOM, KT_FACES, KT_BCENT_VERTEX, KT_DIV_EDGE, KT_N
 };
 const char* const kt_names[KT_N] = {"prim2con", "c2p", "fill_ghosts", "centre_B", "face_x", "face_y",
                                     "face_z", "cell", "vertex", "edge", "rk_stage", "zero", "adjoint", "tmunu",
-                                    "inter_level", "geometry"};
+                                    "inter_level", "geometry", "faces", "centre_B+vertex", "divergence+edge"};
 struct Pending {
   hipEvent_t a, b;
   int kind;
@@ -3497,9 +3498,9 @@ int faces(const GD& g, const asterx_batch* b, const FaceArgs& fa, bool uct, hipS
   return face_launch<D, ASTERX_RECON_WENOZ>(g, b, fa, uct, s);
 }
 
-// All directions in one launch: no direction waits for another's last wavefronts (RK4 steps with the directions
-// in launches of their own and in one: 64^3, PPM, 0.811 and 0.728 ms; 97 x 61 x 45, MP5, upwind CT, 1.194 and
-// 1.050; 96^3, WENO-Z, 2.49 and 2.37; 128^3, PPM, 5.06 and 5.02).
+// All directions in one launch: no direction waits for another's last wavefronts.  RK4 steps from a graph with
+// stored geometry, the directions apart and in one launch: 32^3, PPM, 0.275 and 0.203 ms; 64^3 0.798 and 0.709;
+// 96^3 2.276 and 2.188; 128^3 5.018 and 4.925; 192^3 15.82 and 15.78; 64^3, MP5, upwind CT, 1.098 and 0.978.
 template <int R>
 int faces_joint(const GD& g, FaceArgs fa, bool uct, hipStream_t s) {
   const int lo = uct ? 3 : 1;
@@ -3508,10 +3509,11 @@ int faces_joint(const GD& g, FaceArgs fa, bool uct, hipStream_t s) {
     fa.rows[d] = face_rows(g.n, d, lo, face_march<R>());
     c[d] = face_items(g.n, d, lo, fa.rows[d]);
   }
-  const dim3 all(c[0] + c[1] + c[2]);
-  if (uct) hipLaunchKernelGGL((k_faces<R, true>), all, dim3(64), 0, s, g, fa, c[0], c[1]);
-  else hipLaunchKernelGGL((k_faces<R, false>), all, dim3(64), 0, s, g, fa, c[0], c[1]);
-  return launched();
+  return timed(KT_FACES, s, [&] {
+    const dim3 all(c[0] + c[1] + c[2]);
+    if (uct) hipLaunchKernelGGL((k_faces<R, true>), all, dim3(64), 0, s, g, fa, c[0], c[1]);
+    else hipLaunchKernelGGL((k_faces<R, false>), all, dim3(64), 0, s, g, fa, c[0], c[1]);
+  });
 }
 int all_faces(const GD& g, const FaceArgs& fa, bool uct, hipStream_t s) {
   if (fa.recon == ASTERX_RECON_MINMOD) return faces_joint<ASTERX_RECON_MINMOD>(g, fa, uct, s);
@@ -3644,13 +3646,14 @@ int do_rhs(const GD& g, const asterx_batch* b, const asterx_params* p, const dou
   double* fp = ws + 25 * g.N;
   double* apm = ws + 28 * g.N;
   const bool uct = p->ct == ASTERX_CT_UCT;
-  // With stored geometry phases share launches (kernel timing keeps them apart: its classes are phases).
-  const bool joint = geo && !b && !g_timing, lorenz = p->gauge == ASTERX_GAUGE_LORENZ;
+  // With stored geometry phases share launches.
+  const bool joint = geo && !b, lorenz = p->gauge == ASTERX_GAUGE_LORENZ;
   const VertexArgs va{metric, A, psi, ga, fp};
   if (joint && lorenz) {
     const unsigned n0 = tiles_for(PH_BCENT, g), n1 = tiles_for(PH_VERTEX, g);
-    hipLaunchKernelGGL(k_bcent_vertex, dim3(n0 + n1), dim3(256), 0, s, g, A, bc, va, n0);
-    rc = launched();
+    rc = timed(KT_BCENT_VERTEX, s, [&] {
+      hipLaunchKernelGGL(k_bcent_vertex, dim3(n0 + n1), dim3(256), 0, s, g, A, bc, va, n0);
+    });
   } else {
     rc = RUN_PHASE(KT_BCENT, PH_BCENT, k_bcent, kb_bcent, A, bc);
   }
@@ -3703,9 +3706,10 @@ int do_rhs(const GD& g, const asterx_batch* b, const asterx_params* p, const dou
   if (joint) {
     const DivArgs da{src, flux, A, rhs, red, cmb};
     const unsigned n0 = box_blocks<64, 4>(g.n), n1 = tiles_for(PH_EDGE, g);
-    if (uct) hipLaunchKernelGGL(k_div_edge<true>, dim3(n0 + n1), dim3(256), 0, s, g, da, ea, n0);
-    else hipLaunchKernelGGL(k_div_edge<false>, dim3(n0 + n1), dim3(256), 0, s, g, da, ea, n0);
-    return launched();
+    return timed(KT_DIV_EDGE, s, [&] {
+      if (uct) hipLaunchKernelGGL(k_div_edge<true>, dim3(n0 + n1), dim3(256), 0, s, g, da, ea, n0);
+      else hipLaunchKernelGGL(k_div_edge<false>, dim3(n0 + n1), dim3(256), 0, s, g, da, ea, n0);
+    });
   }
   if (src) {
     const DivArgs da{src, flux, A, rhs, red, cmb};

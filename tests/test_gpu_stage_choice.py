@@ -44,3 +44,28 @@ def test_at_time_overridden_in_place(ax, rk):
         blk.run(2)
     torch.cuda.synchronize()
     assert torch.equal(a.state, b.state) and torch.equal(a.prim, b.prim) and torch.equal(a.red, b.red)
+
+
+@pytest.mark.parametrize("ct,gauge", [("fct", "lorenz"), ("uct", "algebraic")])
+def test_timing_does_not_change_what_runs(ax, ct, gauge):
+    """Steps with per-kernel timing on equal those without bit for bit, and the classes are those of the launches the
+    untimed steps make: the faces' directions in one, the divergence with the edges, the centre field with the gauge
+    quantities where there are any."""
+    import torch
+    w = W.curved_block(seed=72, n=(20, 13, 11), recon="ppm", nsteps=2, rk=4, ng=4)
+    w.params.update(ct=ct, gauge=gauge)
+    print("case timing", ct, gauge, flush=True)
+    a, b = ax.Block(w), ax.Block(w)
+    a.run(2)
+    ax.timing_reset()
+    ax.timing_enable(True)
+    try:
+        b.run(2)
+        torch.cuda.synchronize()
+        kt = ax.timing_read()
+    finally:
+        ax.timing_enable(False)
+    assert torch.equal(a.state, b.state) and torch.equal(a.prim, b.prim) and torch.equal(a.red, b.red)
+    ran = {k: v[1] for k, v in kt.items() if v[1] > 0}
+    first = "centre_B+vertex" if gauge == "lorenz" else "centre_B"
+    assert ran == {"geometry": 2, "c2p": 8, "fill_ghosts": 16, first: 8, "faces": 8, "divergence+edge": 8}
