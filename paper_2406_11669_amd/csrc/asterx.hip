@@ -1480,22 +1480,26 @@ DEV void face_side(const GD& g, const FaceArgs& fa, const Geo& G, double Bn, int
 struct FaceIn {
   double m[10], Bn;
 };
-template <int D>
+// Without stored metric: gathered from the 16 vertices around the face, in geom_wave's order of passes (the lower
+// axis first), so that both give the same bits and blocks may choose by size.
+template <int D, int RECON>
 DEV void face_load(const GD& g, const FaceArgs& fa, int id, FaceIn& f, bool stored = true) {
-  constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
   if (fa.fma[D] && stored) {
 #pragma unroll
     for (int q = 0; q < 10; ++q) f.m[q] = ldu(q < 7 ? fa.fma[D] + (size_t)q * g.N : fa.fmb[D] + (size_t)(q - 7) * g.N, id);
   } else {
-    const int st[3] = {1, g.sy, g.sz};
-#pragma unroll 1
+    const int s1 = D == 0 ? g.sy : 1, s2 = D == 2 ? g.sy : g.sz;
+    // two components in flight where the reconstruction leaves registers for them (asterx_rhs, 64^3: MINMOD 166 ->
+    // 162 us; PPM 168 -> 176, MP5 192 -> 201)
+    constexpr int NQ = RECON == ASTERX_RECON_MINMOD ? 2 : 1;
+#pragma unroll NQ
     for (int q = 0; q < 10; ++q) {
-      const double* p = fa.metric + (size_t)q * g.N + (id - st[t1] - st[t2]);
+      const double* p = fa.metric + (size_t)q * g.N + (id - s1 - s2);
       double r[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const double* row = p + k * st[t2];
-        r[k] = lag(row[0], row[st[t1]], row[2 * st[t1]], row[3 * st[t1]]);
+        const double* row = p + k * s2;
+        r[k] = lag(row[0], row[s1], row[2 * s1], row[3 * s1]);
       }
       const double v = lag(r[0], r[1], r[2], r[3]);
 #pragma unroll
@@ -1611,7 +1615,7 @@ DEV void face_wave_x(const GD& g, const FaceArgs& fa, unsigned item, FaceLDS& L)
   const int id = at(g, c[0], c[1], c[2]);
   double XL[7], XR[7], smax = 0.0;
   FaceIn fin;
-  face_load<0>(g, fa, id, fin, !fa.xown || (c[1] >= 0 && c[2] >= 0));
+  face_load<0, RECON>(g, fa, id, fin, !fa.xown || (c[1] >= 0 && c[2] >= 0));
   cell_faces<0, RECON>(g, fa, id, XR, L.hi, L.lo);
   wave_lds_sync();
   if (__lane_id() > 0 && item * 63 + __lane_id() < total && c[0] >= 0) {
@@ -1651,7 +1655,7 @@ DEV void face_wave_yz(const GD& g, const FaceArgs& fa, unsigned item, FaceLDS& L
     wave_lds_sync();
     if (j >= j0 && in) {
       FaceIn fin;
-      face_load<D>(g, fa, id, fin);
+      face_load<D, RECON>(g, fa, id, fin);
       smax = fmax(smax, face_solve<D, UCT>(g, fa, id, fin, XL, XR));
     }
   }
@@ -2454,7 +2458,6 @@ __global__ __launch_bounds__(256) void kb_cell(const PatchDesc* __restrict__ P, 
   }
 }
 
-__global__ __launch_bounds__(256) void k_div(GD g, DivArgs da) { div_body(g, da, my_tile()); }
 __global__ __launch_bounds__(256) void k_vertex(GD g, VertexArgs va) { vertex_body(g, va, my_tile()); }
 __global__ __launch_bounds__(256) void k_tmunu(GD g, TmunuArgs ta) {
   __shared__ TmunuLDS L;
@@ -3498,16 +3501,16 @@ int faces(const GD& g, const asterx_batch* b, const FaceArgs& fa, bool uct, hipS
   return face_launch<D, ASTERX_RECON_WENOZ>(g, b, fa, uct, s);
 }
 
-// All directions in one launch: no direction waits for another's last wavefronts.  RK4 steps from a graph with
-// stored geometry, the directions apart and in one launch: 32^3, PPM, 0.275 and 0.203 ms; 64^3 0.798 and 0.709;
+// The first nd directions in one launch: no direction waits for another's last wavefronts.  RK4 steps from a graph
+// with stored geometry, the directions apart and in one launch: 32^3, PPM, 0.275 and 0.203 ms; 64^3 0.798 and 0.709;
 // 96^3 2.276 and 2.188; 128^3 5.018 and 4.925; 192^3 15.82 and 15.78; 64^3, MP5, upwind CT, 1.098 and 0.978.
 template <int R>
-int faces_joint(const GD& g, FaceArgs fa, bool uct, hipStream_t s) {
+int faces_joint(const GD& g, FaceArgs fa, bool uct, hipStream_t s, int nd) {
   const int lo = uct ? 3 : 1;
   unsigned c[3];
   for (int d = 0; d < 3; ++d) {
     fa.rows[d] = face_rows(g.n, d, lo, face_march<R>());
-    c[d] = face_items(g.n, d, lo, fa.rows[d]);
+    c[d] = d < nd ? face_items(g.n, d, lo, fa.rows[d]) : 0;
   }
   return timed(KT_FACES, s, [&] {
     const dim3 all(c[0] + c[1] + c[2]);
@@ -3515,11 +3518,29 @@ int faces_joint(const GD& g, FaceArgs fa, bool uct, hipStream_t s) {
     else hipLaunchKernelGGL((k_faces<R, false>), all, dim3(64), 0, s, g, fa, c[0], c[1]);
   });
 }
-int all_faces(const GD& g, const FaceArgs& fa, bool uct, hipStream_t s) {
-  if (fa.recon == ASTERX_RECON_MINMOD) return faces_joint<ASTERX_RECON_MINMOD>(g, fa, uct, s);
-  if (fa.recon == ASTERX_RECON_PPM) return faces_joint<ASTERX_RECON_PPM>(g, fa, uct, s);
-  if (fa.recon == ASTERX_RECON_MP5) return faces_joint<ASTERX_RECON_MP5>(g, fa, uct, s);
-  return faces_joint<ASTERX_RECON_WENOZ>(g, fa, uct, s);
+int first_faces(const GD& g, const FaceArgs& fa, bool uct, hipStream_t s, int nd) {
+  if (fa.recon == ASTERX_RECON_MINMOD) return faces_joint<ASTERX_RECON_MINMOD>(g, fa, uct, s, nd);
+  if (fa.recon == ASTERX_RECON_PPM) return faces_joint<ASTERX_RECON_PPM>(g, fa, uct, s, nd);
+  if (fa.recon == ASTERX_RECON_MP5) return faces_joint<ASTERX_RECON_MP5>(g, fa, uct, s, nd);
+  return faces_joint<ASTERX_RECON_WENOZ>(g, fa, uct, s, nd);
+}
+
+// Whether a block without stored geometry gathers its face metric instead of interpolating it into the workspace
+// first: then nothing waits for the interpolation, all directions and the centre field with the gauge quantities share
+// launches, but every face reads 160 values.  Small blocks are bound by the launches, large ones by those reads: the
+// line is at a count of faces (asterx_rhs from a graph, interpolated and gathered: PPM, 24^3, 73 and 56 us; 64^3 187
+// and 172; 88^3, 2.12e6 faces, 444 and 428; 96^3, 2.74e6, 557 and 562; 128^3 1253 and 1385; upwind CT, PPM, 80^3,
+// 1.76e6, 397 and 389; 88^3, 2.31e6, 526 and 525; 400 x 200 x 6, 2.38e6, 484 and 505; MINMOD, whose faces cost less
+// beside the reads, 64^3, 0.82e6, 169 and 166; 80^3, 1.59e6, 307 and 315; 128^3 1174 and 1433).
+bool face_gather(const GD& g, const asterx_params* p) {
+  const int lo = p->ct == ASTERX_CT_UCT ? 3 : 1;
+  long long e[3], f[3];
+  for (int a = 0; a < 3; ++a) {
+    e[a] = g.n[a] + 2 * lo - 1;
+    f[a] = g.n[a] + 1;
+  }
+  const long long faces = f[0] * e[1] * e[2] + e[0] * f[1] * e[2] + e[0] * e[1] * f[2];
+  return faces <= (p->recon == ASTERX_RECON_MINMOD ? 5LL << 18 : 9LL << 18);
 }
 
 // Interpolated spacetime data of the sets in MASK.
@@ -3632,9 +3653,10 @@ int do_bcent(const GD& g, const double* A, double* bc, hipStream_t s) {
 
 // src (single blocks): densitized sources stored by a recovery with sources; the cell phase is
 // then the divergence kernel instead of the cell kernel.  The face metric comes from geo (all directions,
-// as stored by asterx_geometry), for x faces from xfm (as stored by asterx_c2p_src), or is interpolated
-// here into parts of the workspace that hold nothing at that time: the fluxes of directions not yet done,
-// the gauge quantities (written after the faces) and, under flux CT, the nine fields of upwind CT.
+// as stored by asterx_geometry), for x faces from xfm (as stored by asterx_c2p_src), is gathered by the faces
+// (face_gather), or is interpolated here into parts of the workspace that hold nothing at that time: the fluxes of
+// directions not yet done, the gauge quantities (written after the faces) and, under flux CT, the nine fields of
+// upwind CT.  Phases of a single block that don't depend on each other share launches.
 int do_rhs(const GD& g, const asterx_batch* b, const asterx_params* p, const double* metric, const double* curv,
            const double* prim, const double* A, const double* psi, double dt_max, double* rhs, double* red,
            double* ws, hipStream_t s, const Combine& cmb = Combine{}, const double* src = nullptr,
@@ -3645,11 +3667,12 @@ int do_rhs(const GD& g, const asterx_batch* b, const asterx_params* p, const dou
   double* ga = ws + 24 * g.N;
   double* fp = ws + 25 * g.N;
   double* apm = ws + 28 * g.N;
-  const bool uct = p->ct == ASTERX_CT_UCT;
-  // With stored geometry phases share launches.
-  const bool joint = geo && !b, lorenz = p->gauge == ASTERX_GAUGE_LORENZ;
+  const bool uct = p->ct == ASTERX_CT_UCT, lorenz = p->gauge == ASTERX_GAUGE_LORENZ;
+  const bool gather = !b && !geo && face_gather(g, p);
+  const bool staged = !geo && !gather;  // the workspace holds face metric until the faces are done
   const VertexArgs va{metric, A, psi, ga, fp};
-  if (joint && lorenz) {
+  const bool gauge_first = lorenz && !b && !staged;
+  if (gauge_first) {
     const unsigned n0 = tiles_for(PH_BCENT, g), n1 = tiles_for(PH_VERTEX, g);
     rc = timed(KT_BCENT_VERTEX, s, [&] {
       hipLaunchKernelGGL(k_bcent_vertex, dim3(n0 + n1), dim3(256), 0, s, g, A, bc, va, n0);
@@ -3667,6 +3690,11 @@ int do_rhs(const GD& g, const asterx_batch* b, const asterx_params* p, const dou
     fa.fma[d] = gm.fa[d];
     fa.fmb[d] = gm.fb[d];
   };
+  if (xfm && !uct) {
+    fa.xown = true;
+    fa.fma[0] = xfm;
+    fa.fmb[0] = xfm + 7 * g.N;
+  }
   // workspace fields: x fluxes 3..9, y 10..16, z 17..23, gauge 24..27, upwind CT 28..30 (x), 31..33 (y), 34..36 (z)
   bool later_z = false;
   if (geo) {
@@ -3674,14 +3702,12 @@ int do_rhs(const GD& g, const asterx_batch* b, const asterx_params* p, const dou
       fa.fma[d] = geo + (size_t)(10 * d) * g.N;
       fa.fmb[d] = fa.fma[d] + 7 * g.N;
     }
+  } else if (gather) {
   } else if (uct) {
     put(0, 10, 17);
     put(1, 20, 34);
     if ((rc = geometry<GM_X | GM_Y>(g, b, gm, s))) return rc;  // z faces gather theirs: no ten fields are free then
   } else if (xfm) {
-    fa.xown = true;
-    fa.fma[0] = xfm;
-    fa.fmb[0] = xfm + 7 * g.N;
     put(1, 17, 34);
     put(2, 24, 31);
     if ((rc = geometry<GM_Y | GM_Z>(g, b, gm, s))) return rc;
@@ -3691,11 +3717,16 @@ int do_rhs(const GD& g, const asterx_batch* b, const asterx_params* p, const dou
     later_z = true;
     if ((rc = geometry<GM_X | GM_Y>(g, b, gm, s))) return rc;
   }
-  if (joint) {
-    if ((rc = all_faces(g, fa, uct, s))) return rc;
+  if (!b && !staged) {
+    if ((rc = first_faces(g, fa, uct, s, 3))) return rc;
   } else {
-    if ((rc = faces<0>(g, b, fa, uct, s))) return rc;
-    if ((rc = faces<1>(g, b, fa, uct, s))) return rc;
+    // x and y faces share a launch where neither's output lies over the other's metric
+    if (!b && !uct) {
+      if ((rc = first_faces(g, fa, uct, s, 2))) return rc;
+    } else {
+      if ((rc = faces<0>(g, b, fa, uct, s))) return rc;
+      if ((rc = faces<1>(g, b, fa, uct, s))) return rc;
+    }
     if (later_z) {
       put(2, 24, 31);
       if ((rc = geometry<GM_Z>(g, b, gm, s))) return rc;
@@ -3703,7 +3734,9 @@ int do_rhs(const GD& g, const asterx_batch* b, const asterx_params* p, const dou
     if ((rc = faces<2>(g, b, fa, uct, s))) return rc;
   }
   EdgeArgs ea{metric, psi, flux, ga, fp, rhs, p->xi / dt_max, p->gauge, cmb, apm};
-  if (joint) {
+  auto gauge = [&] { return RUN_PHASE(KT_VERTEX, PH_VERTEX, k_vertex, kb_vertex, va); };
+  if (src) {
+    if (lorenz && !gauge_first && (rc = gauge())) return rc;
     const DivArgs da{src, flux, A, rhs, red, cmb};
     const unsigned n0 = box_blocks<64, 4>(g.n), n1 = tiles_for(PH_EDGE, g);
     return timed(KT_DIV_EDGE, s, [&] {
@@ -3711,17 +3744,9 @@ int do_rhs(const GD& g, const asterx_batch* b, const asterx_params* p, const dou
       else hipLaunchKernelGGL(k_div_edge<false>, dim3(n0 + n1), dim3(256), 0, s, g, da, ea, n0);
     });
   }
-  if (src) {
-    const DivArgs da{src, flux, A, rhs, red, cmb};
-    if ((rc = timed(KT_CELL, s, [&] {
-           hipLaunchKernelGGL(k_div, dim3(box_blocks<64, 4>(g.n)), dim3(256), 0, s, g, da);
-         })))
-      return rc;
-  } else {
-    CellArgs ca{metric, curv, prim, A, bc, flux, rhs, red, p->gamma, cmb};
-    if ((rc = RUN_PHASE(KT_CELL, PH_CELL, k_cell, kb_cell, ca))) return rc;
-  }
-  if (lorenz && (rc = RUN_PHASE(KT_VERTEX, PH_VERTEX, k_vertex, kb_vertex, va))) return rc;
+  CellArgs ca{metric, curv, prim, A, bc, flux, rhs, red, p->gamma, cmb};
+  if ((rc = RUN_PHASE(KT_CELL, PH_CELL, k_cell, kb_cell, ca))) return rc;
+  if (lorenz && !gauge_first && (rc = gauge())) return rc;
   if (uct)
     return timed(KT_EDGE, s, [&] {
       hipLaunchKernelGGL(k_edge_uct, dim3(tiles_for(PH_EDGE, g)), dim3(256), 0, s, g, ea);

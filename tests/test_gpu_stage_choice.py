@@ -3,8 +3,12 @@ import numpy as np
 import pytest
 
 from paper_2406_11669_amd import workloads as W
+from tests.parity import assert_fields_close
 
 pytestmark = pytest.mark.gpu
+
+STATE_NAMES = ["D", "Sx", "Sy", "Sz", "tau", "Ax", "Ay", "Az", "Psi"]
+PRIM_NAMES = ["rho", "p", "vx", "vy", "vz"]
 
 
 @pytest.fixture(scope="module")
@@ -69,3 +73,63 @@ def test_timing_does_not_change_what_runs(ax, ct, gauge):
     ran = {k: v[1] for k, v in kt.items() if v[1] > 0}
     first = "centre_B+vertex" if gauge == "lorenz" else "centre_B"
     assert ran == {"geometry": 2, "c2p": 8, "fill_ghosts": 16, first: 8, "faces": 8, "divergence+edge": 8}
+
+
+PLAIN = [("minmod", (20, 13, 11)), ("ppm", (62, 5, 7)), ("wenoz", (5, 63, 4)), ("mp5", (9, 8, 33)),
+         ("minmod", (520, 100, 8)), ("ppm", (520, 170, 8)), ("mp5", (9, 300, 270))]
+
+
+def _gathers(recon, ct, n):
+    """The library's rule for blocks without stored geometry: a count of faces."""
+    lo = 3 if ct == "uct" else 1
+    faces = sum(np.prod([n[a] + (1 if a == d else 2 * lo - 1) for a in range(3)]) for d in range(3))
+    return faces <= (5 if recon == "minmod" else 9) * 2 ** 18
+
+
+@pytest.mark.parametrize("recon,n", PLAIN)
+def test_gathered_and_interpolated_face_metric(ax, recon, n):
+    """asterx_rhs of a block, whose faces gather their metric up to a count of faces and read it as interpolated
+    above, against a batch of that block alone, which always interpolates: the same bits."""
+    import torch
+    w = W.curved_block(seed=73, n=n, recon=recon, nsteps=1)
+    print("case gathered metric", recon, n, flush=True)
+    assert _gathers(recon, "fct", n) == (PLAIN.index((recon, n)) < 4)
+    a, b = ax.Block(w, fused=False), ax.Batch([w], fused=False)
+    outs = []
+    for x in (a, b):
+        out = torch.zeros_like(x.state)
+        x.eval_rhs(x.state, out)
+        outs.append(out.reshape(9, -1)[:, :w.layout.npts].cpu().numpy().reshape((9,) + w.layout.shape3))
+    torch.cuda.synchronize()
+    assert np.array_equal(w.layout.owned(outs[0]), w.layout.owned(outs[1]))
+    assert torch.equal(a.red, b.red)
+
+
+@pytest.mark.parametrize("recon,ct,n", [("ppm", "fct", (520, 170, 8)), ("minmod", "fct", (7, 300, 190)),
+                                        ("ppm", "uct", (8, 300, 220)), ("wenoz", "uct", (300, 220, 8))])
+def test_large_blocks_without_stored_geometry(ax, recon, ct, n):
+    """Blocks beyond the size up to which faces gather their metric: asterx_rhs_rk and asterx_rhs_rk_src against the
+    stored geometry, within 1e-13 of the fields' scales (they differ in the order of the interpolation's passes)."""
+    import torch
+    w = W.curved_block(seed=74, n=n, recon=recon, nsteps=1, ng=4)
+    w.params["ct"] = ct
+    L = w.layout
+    assert not _gathers(recon, ct, n)
+    print("case large without geometry", recon, ct, n, flush=True)
+    z = lambda nf: torch.zeros((nf,) + L.shape3, dtype=torch.float64, device="cuda")
+    blk = ax.Block(w, src_in_c2p=False)
+    src, src4, geo = z(ax.SRC_FIELDS), z(4), z(ax.GEO_FIELDS)
+    U, P, M = blk.state, blk.prim, blk.metric
+    ax.c2p_src(L, w.params, M, blk.curv, U[5:8], U[0:5], P.clone(), src)
+    ax.geometry(L, w.params, M, blk.curv, geo)
+    ax.c2p_geo(L, w.params, geo, U[5:8], U[0:5], P, src4)
+    ax.fill_ghosts(L, P, w.bc_cell)
+    outs = [z(9) for _ in range(3)]
+    rk = lambda o: [([1.0], [U], w.dt, o)]
+    ax.rhs_rk_geo(L, w.params, M, geo, P, U[5:8], U[8:9], src4, w.dt, rk(outs[0]), blk.red, blk.ws)
+    ax.rhs_rk(L, w.params, M, blk.curv, P, U[5:8], U[8:9], w.dt, rk(outs[1]), blk.red, blk.ws)
+    ax.rhs_rk_src(L, w.params, M, P, U[5:8], U[8:9], src, w.dt, rk(outs[2]), blk.red, blk.ws)
+    torch.cuda.synchronize()
+    ref = outs[0].cpu().numpy()
+    for o in outs[1:]:
+        assert_fields_close(o.cpu().numpy(), ref, 1e-13, L.owned, STATE_NAMES)
