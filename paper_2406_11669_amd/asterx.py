@@ -508,10 +508,18 @@ class Block:
     RK2 is Heun's method, RK4 the classical scheme (accumulator form).  With fused=True (the
     default) the right-hand side goes straight into the stage outputs (asterx_rhs_rk; RK4
     alternates two stage buffers so that no output is the state being evaluated); fused=False
-    stores it and combines with asterx_rk_stage.  In the fused form the metric is interpolated to
-    faces and centres once per step (once per stage metric with metric_fn; asterx_geometry) and the
-    geometric sources are evaluated by the recovery kernel (asterx_c2p_geo + asterx_rhs_rk_geo),
-    unless src_in_c2p is False (asterx_c2p + asterx_rhs_rk).  The two agree up to rounding."""
+    stores it and combines with asterx_rk_stage.  In the fused form the geometric sources are
+    evaluated by the recovery kernel, unless src_in_c2p is False (asterx_c2p + asterx_rhs_rk).  A metric
+    that several stages of a step share is interpolated to faces and centres once for them
+    (asterx_geometry, asterx_c2p_geo + asterx_rhs_rk_geo); one that serves a single stage only on small
+    blocks (else asterx_c2p_src + asterx_rhs_rk_src).  All forms agree up to rounding."""
+
+    # Cells up to which a single stage interpolates the spacetime data first.  Small stages are bound by their
+    # launches and the recovery's chain of interpolation passes, large ones by the stores of the 76 fields (a PPM stage
+    # from a graph, interpolated first and by the recovery with sources: 32^3 58 and 71 us, 48^3 106 and 104, 56^3 148
+    # and 150, 64^3 214 and 189, 128^3 1502 and 1361; two stages together 48^3 173 and 204, 64^3 357 and 373, 128^3
+    # 2524 and 2714).
+    ONE_STAGE_GEO_CELLS = 1 << 17
 
     def __init__(self, wl, device="cuda", fused=True, metric_fn=None, src_in_c2p=True):
         self.fused = fused
@@ -545,7 +553,8 @@ class Block:
                 pass  # blocks without room for the stored geometry interpolate it in every stage
             self.src = torch.zeros((SRC_FIELDS if self.geo is None else 4,) + self.L.shape3, dtype=torch.float64,
                                    device=dev)
-        self._stepping = self._geo_held = False  # geo holds the current metric's data (inside a step only)
+        self._shared = 1  # stages that the current metric serves (more than one inside a step only)
+        self._geo_held = False  # geo holds the current metric's data (inside a step only)
         self.red = torch.zeros(2, dtype=torch.float64, device=dev)
         self.stats = torch.zeros(6, dtype=torch.int64, device=dev)
         self.flags = torch.zeros(self.L.shape3, dtype=torch.uint8, device=dev)
@@ -562,11 +571,16 @@ class Block:
         if self.metric_fn is not None:
             self.metric, self.curv = self.metric_fn(t)
 
-    def _at_time(self, t):
+    def _metric_fixed(self):
+        """Whether no hook may change the metric within a step (also in place): neither metric_fn nor a subclass."""
+        return self.metric_fn is None and getattr(self.at_time, "__func__", None) is Block.at_time
+
+    def _at_time(self, t, stages):
+        """Before `stages` stages at time t."""
         self.at_time(t)
-        # a metric_fn or a subclass's at_time may have changed the metric, also in place
-        if self.metric_fn is not None or getattr(self.at_time, "__func__", None) is not Block.at_time:
+        if not self._metric_fixed():
             self._geo_held = False
+            self._shared = stages
 
     def recover(self, U):
         """c2p on U (in place for atmosphere cells) and the primitives' ghosts."""
@@ -579,24 +593,30 @@ class Block:
         rhs(self.L, self.params, self.metric, self.curv, self.prim, U[5:8], U[8:9], self.dt, out, self.red,
             self.ws)
 
+    def _takes_geometry(self):
+        n = self.L.n
+        return self.geo is not None and (self._shared > 1 or n[0] * n[1] * n[2] <= self.ONE_STAGE_GEO_CELLS)
+
     def stage(self, U, outs):
         """c2p on U, then its right-hand side combined into outs = [(a, us, b_dt, out)]."""
-        if self.src_in_c2p and self.geo is None:
-            c2p_src(self.L, self.params, self.metric, self.curv, U[5:8], U[0:5], self.prim, self.src, self.flags,
-                    self.stats, mlp=self.mlp)
-            fill_ghosts(self.L, self.prim, self.wl.bc_cell)
-            rhs_rk_src(self.L, self.params, self.metric, self.prim, U[5:8], U[8:9], self.src, self.dt, outs, self.red,
-                       self.ws)
-            return
-        if self.src_in_c2p:
+        if self.src_in_c2p and self._takes_geometry():
             if not self._geo_held:
                 geometry(self.L, self.params, self.metric, self.curv, self.geo)
-                self._geo_held = self._stepping
+                self._geo_held = self._shared > 1
             c2p_geo(self.L, self.params, self.geo, U[5:8], U[0:5], self.prim, self.src, self.flags, self.stats,
                     mlp=self.mlp)
             fill_ghosts(self.L, self.prim, self.wl.bc_cell)
             rhs_rk_geo(self.L, self.params, self.metric, self.geo, self.prim, U[5:8], U[8:9], self.src, self.dt, outs,
                        self.red, self.ws)
+            return
+        if self.src_in_c2p:
+            # the x-face metric goes where the stored geometry, unused then, would lie
+            src = self.src if self.geo is None else self.geo[:SRC_FIELDS]
+            c2p_src(self.L, self.params, self.metric, self.curv, U[5:8], U[0:5], self.prim, src, self.flags,
+                    self.stats, mlp=self.mlp)
+            fill_ghosts(self.L, self.prim, self.wl.bc_cell)
+            rhs_rk_src(self.L, self.params, self.metric, self.prim, U[5:8], U[8:9], src, self.dt, outs, self.red,
+                       self.ws)
             return
         self.recover(U)
         rhs_rk(self.L, self.params, self.metric, self.curv, self.prim, U[5:8], U[8:9], self.dt, outs, self.red,
@@ -604,14 +624,14 @@ class Block:
 
     def step(self):
         # the metric is the caller's between steps: what the last one interpolated is not kept
-        self._stepping, self._geo_held = True, False
+        self._shared, self._geo_held = self.stages_per_step if self._metric_fixed() else 1, False
         try:
             if self.fused:
                 self._step_fused()
             else:
                 self._step_stored()
         finally:
-            self._stepping = self._geo_held = False
+            self._shared, self._geo_held = 1, False
         self.t += self.dt
 
     def _step_fused(self):
@@ -619,23 +639,23 @@ class Block:
         U0 = self.state
         if self.wl.rk == 2:
             U1 = self.tmp
-            self._at_time(t)
+            self._at_time(t, 1)
             self.stage(U0, [([1.0], [U0], dt, U1)])
             self.fill_state(U1)
-            self._at_time(t + dt)
+            self._at_time(t + dt, 1)
             self.stage(U1, [([0.5, 0.5], [U0, U1], 0.5 * dt, U0)])
             self.fill_state(U0)
         else:
             Ua, Ub, acc = self.tmp, self.tmp2, self.acc
-            self._at_time(t)
+            self._at_time(t, 1)
             self.stage(U0, [([1.0], [U0], dt / 6.0, acc), ([1.0], [U0], 0.5 * dt, Ua)])
             self.fill_state(Ua)
-            self._at_time(t + 0.5 * dt)
+            self._at_time(t + 0.5 * dt, 2)
             self.stage(Ua, [([1.0], [acc], dt / 3.0, acc), ([1.0], [U0], 0.5 * dt, Ub)])
             self.fill_state(Ub)
             self.stage(Ub, [([1.0], [acc], dt / 3.0, acc), ([1.0], [U0], dt, Ua)])
             self.fill_state(Ua)
-            self._at_time(t + dt)
+            self._at_time(t + dt, 1)
             self.stage(Ua, [([1.0], [acc], dt / 6.0, U0)])
             self.fill_state(U0)
 
@@ -644,22 +664,22 @@ class Block:
         U0, K = self.state, self.k
         if self.wl.rk == 2:
             U1 = self.tmp
-            self._at_time(t)
+            self._at_time(t, 1)
             self.eval_rhs(U0, K)
             rk_stage(self.L, [1.0], [U0], dt, K, U1)
             self.fill_state(U1)
-            self._at_time(t + dt)
+            self._at_time(t + dt, 1)
             self.eval_rhs(U1, K)
             rk_stage(self.L, [0.5, 0.5], [U0, U1], 0.5 * dt, K, U0)
             self.fill_state(U0)
         else:
             Ut, acc = self.tmp, self.acc
-            self._at_time(t)
+            self._at_time(t, 1)
             self.eval_rhs(U0, K)
             rk_stage(self.L, [1.0], [U0], 0.5 * dt, K, Ut)
             rk_stage(self.L, [1.0], [U0], dt / 6.0, K, acc)
             self.fill_state(Ut)
-            self._at_time(t + 0.5 * dt)
+            self._at_time(t + 0.5 * dt, 2)
             self.eval_rhs(Ut, K)
             rk_stage(self.L, [1.0], [acc], dt / 3.0, K, acc)
             rk_stage(self.L, [1.0], [U0], 0.5 * dt, K, Ut)
@@ -668,7 +688,7 @@ class Block:
             rk_stage(self.L, [1.0], [acc], dt / 3.0, K, acc)
             rk_stage(self.L, [1.0], [U0], dt, K, Ut)
             self.fill_state(Ut)
-            self._at_time(t + dt)
+            self._at_time(t + dt, 1)
             self.eval_rhs(Ut, K)
             rk_stage(self.L, [1.0], [acc], dt / 6.0, K, U0)
             self.fill_state(U0)

@@ -133,3 +133,91 @@ def test_large_blocks_without_stored_geometry(ax, recon, ct, n):
     ref = outs[0].cpu().numpy()
     for o in outs[1:]:
         assert_fields_close(o.cpu().numpy(), ref, 1e-13, L.owned, STATE_NAMES)
+
+
+def test_rk4_with_metric_fn_vs_oracle(ax, orc):
+    """RK4 steps in a metric that changes with time (the two middle stages share one) against the same stages driven
+    through the oracle, within 1e-10 (the bound of the other parity tests of whole steps)."""
+    import torch
+    w = W.curved_block(seed=76, n=(16, 12, 10), recon="ppm", nsteps=2, rk=4)
+    L, P, dt = w.layout, w.params, w.dt
+    print("case RK4 metric_fn", flush=True)
+    blk = ax.Block(w, metric_fn=lambda t: (torch.from_numpy(_lapse(w, t)).cuda(), torch.from_numpy(w.curv).cuda()))
+    blk.run(2)
+    torch.cuda.synchronize()
+    cons = orc.prim2con(L, P, w.metric, w.A, w.prim)
+    orc.fill_ghosts(L, cons, w.bc_cell)
+    U, prim = w.state(cons), w.prim.copy()
+
+    def k(V, t):
+        m = _lapse(w, t)
+        orc.c2p(L, P, m, V[5:8], V[0:5], prim)
+        orc.fill_ghosts(L, prim, w.bc_cell)
+        return orc.rhs(L, P, m, w.curv, prim, V[5:8], V[8:9], dt)[0]
+
+    def combine(a, us, b, K):
+        out = U.copy()
+        orc.rk_stage(L, a, us, b, K, out)
+        orc.fill_ghosts(L, out, w.bc_cell)
+        return out
+
+    assert w.A_shift is None and tuple(w.bc_A) == tuple(w.bc_cell)
+    for step in range(2):
+        t = step * dt
+        K = k(U, t)
+        acc, V = combine([1.0], [U], dt / 6.0, K), combine([1.0], [U], 0.5 * dt, K)
+        for b, c, at in ((dt / 3.0, 0.5 * dt, t + 0.5 * dt), (dt / 3.0, dt, t + 0.5 * dt)):
+            K = k(V, at)
+            acc, V = combine([1.0], [acc], b, K), combine([1.0], [U], c, K)
+        U = combine([1.0], [acc], dt / 6.0, k(V, t + dt))
+    assert_fields_close(blk.state.cpu().numpy(), U, 1e-10, L.owned, STATE_NAMES)
+    assert_fields_close(blk.prim.cpu().numpy(), prim, 1e-10, L.owned, PRIM_NAMES)
+
+
+def _counts(ax, fn):
+    """Launches per kernel class of one call of fn."""
+    import torch
+    ax.timing_reset()
+    ax.timing_enable(True)
+    try:
+        fn()
+        torch.cuda.synchronize()
+        kt = ax.timing_read()
+    finally:
+        ax.timing_enable(False)
+    return {k: v[1] for k, v in kt.items() if v[1] > 0}
+
+
+LARGE = (70, 50, 40)  # beyond the cells up to which one stage alone interpolates first
+
+
+@pytest.mark.parametrize("rk,n,geometries", [(4, (16, 12, 10), 3), (2, (16, 12, 10), 2), (4, LARGE, 1), (2, LARGE, 0)])
+def test_metric_fn_steps_choose_by_sharing_stages(ax, rk, n, geometries):
+    """Steps in a metric that changes with time: the two middle stages of RK4 share stored geometry, stages alone take
+    it on small blocks only, and every form agrees with the recovery and right-hand side without it (1e-13 per step of
+    the fields' scales, two steps)."""
+    import torch
+    w = W.curved_block(seed=75, n=n, recon="ppm", nsteps=2, rk=rk)
+    print("case metric_fn forms", rk, n, flush=True)
+    fn = lambda t: (torch.from_numpy(_lapse(w, t)).cuda(), torch.from_numpy(w.curv).cuda())
+    a, b = ax.Block(w, metric_fn=fn), ax.Block(w, metric_fn=fn, src_in_c2p=False)
+    assert (n[0] * n[1] * n[2] <= ax.Block.ONE_STAGE_GEO_CELLS) == (n != LARGE)
+    ran = _counts(ax, a.step)
+    assert _gathers("ppm", "fct", n)  # so that asterx_geometry alone launches the interpolation
+    assert ran.get("geometry", 0) == geometries and ran["c2p"] == ran["faces"] == rk
+    a.step()
+    b.run(2)
+    torch.cuda.synchronize()
+    assert torch.equal(a.stats, b.stats)
+    assert_fields_close(a.state.cpu().numpy(), b.state.cpu().numpy(), 2e-13, w.layout.owned, STATE_NAMES)
+    assert_fields_close(a.prim.cpu().numpy(), b.prim.cpu().numpy(), 2e-13, w.layout.owned, PRIM_NAMES)
+
+
+@pytest.mark.parametrize("n,geometries", [((16, 12, 10), 1), (LARGE, 0)])
+def test_single_stage_form(ax, n, geometries):
+    """A stage called by itself: stored geometry only where interpolating first is the faster form."""
+    w = W.curved_block(seed=77, n=n, recon="ppm", nsteps=1)
+    blk = ax.Block(w)
+    print("case single stage", n, flush=True)
+    ran = _counts(ax, lambda: blk.stage(blk.state, [([1.0], [blk.state], w.dt, blk.tmp)]))
+    assert ran.get("geometry", 0) == geometries and ran["c2p"] == 1
