@@ -521,7 +521,10 @@ class Block:
     # 2524 and 2714).
     ONE_STAGE_GEO_CELLS = 1 << 17
 
-    def __init__(self, wl, device="cuda", fused=True, metric_fn=None, src_in_c2p=True):
+    def __init__(self, wl, device="cuda", fused=True, metric_fn=None, src_in_c2p=True, stored_geometry=None):
+        """stored_geometry: True or False to keep the 76 interpolated fields or to do without them; None keeps them
+        where the device still has room for as much as the rest of the block takes afterwards (a second block, a
+        caller's outputs)."""
         self.fused = fused
         self.src_in_c2p = fused and src_in_c2p
         # a time-dependent spacetime: metric_fn(t) -> (metric, curv) device tensors shaped like the
@@ -545,23 +548,35 @@ class Block:
         self.k = torch.zeros_like(self.state)
         self.tmp2 = torch.zeros_like(self.state) if fused and wl.rk == 4 else None
         self.ws = torch.empty(workspace_size(self.L) // 8, dtype=torch.float64, device=dev)
-        self.src = self.geo = None
-        if self.src_in_c2p:
-            try:
-                self.geo = torch.empty((GEO_FIELDS,) + self.L.shape3, dtype=torch.float64, device=dev)
-            except torch.OutOfMemoryError:
-                pass  # blocks without room for the stored geometry interpolate it in every stage
-            self.src = torch.zeros((SRC_FIELDS if self.geo is None else 4,) + self.L.shape3, dtype=torch.float64,
-                                   device=dev)
         self._shared = 1  # stages that the current metric serves (more than one inside a step only)
         self._geo_held = False  # geo holds the current metric's data (inside a step only)
         self.red = torch.zeros(2, dtype=torch.float64, device=dev)
         self.stats = torch.zeros(6, dtype=torch.int64, device=dev)
         self.flags = torch.zeros(self.L.shape3, dtype=torch.uint8, device=dev)
+        self.src = self.geo = None
+        if self.src_in_c2p:
+            self._allocate_sources(dev, stored_geometry)
         self.dt = wl.dt
         self.mlp = None  # an asterx_mlp (make_mlp) switches every stage's c2p to the learned guess
         prim2con(self.L, self.params, self.metric, self.state[5:8], self.prim, self.state[0:5])
         fill_ghosts(self.L, self.state[0:5], wl.bc_cell)
+
+    def _allocate_sources(self, dev, stored_geometry):
+        """The sources' fields and, with room, the stored geometry; after everything else of the block."""
+        fields = lambda make, nf: make((nf,) + self.L.shape3, dtype=torch.float64, device=dev)
+        if stored_geometry is None:
+            arrays = (self.metric, self.curv, self.prim, self.state, self.tmp, self.acc, self.k, self.tmp2, self.ws)
+            rest = sum(a.numel() for a in arrays if a is not None) + SRC_FIELDS * self.L.npts
+            free = torch.cuda.mem_get_info(dev)[0] + torch.cuda.memory_reserved(dev) - torch.cuda.memory_allocated(dev)
+            stored_geometry = free >= 8 * ((GEO_FIELDS + 4) * self.L.npts + rest)
+        if stored_geometry:
+            try:
+                self.geo = fields(torch.empty, GEO_FIELDS)
+                self.src = fields(torch.zeros, 4)
+                return
+            except torch.OutOfMemoryError:
+                self.geo = None  # blocks without room for the stored geometry interpolate it in every stage
+        self.src = fields(torch.zeros, SRC_FIELDS)
 
     def fill_state(self, U):
         fill_state(self.L, U, self.wl.bc_cell, self.wl.bc_A, self.wl.A_shift)

@@ -221,3 +221,43 @@ def test_single_stage_form(ax, n, geometries):
     print("case single stage", n, flush=True)
     ran = _counts(ax, lambda: blk.stage(blk.state, [([1.0], [blk.state], w.dt, blk.tmp)]))
     assert ran.get("geometry", 0) == geometries and ran["c2p"] == 1
+
+
+@pytest.mark.parametrize("case", ["sources fail", "no reserve", "declined", "asked for"])
+def test_room_for_the_stored_geometry(ax, monkeypatch, case):
+    """Blocks that cannot or shall not keep the stored geometry are made and step through the recovery with sources
+    (within 1e-13 per step of the block that keeps it): an allocation that fails after the geometry's own, a device
+    whose free memory the geometry would use up, the argument that declines it; the argument that asks for it takes it
+    without a reserve."""
+    import torch
+    w = W.curved_block(seed=78, n=(18, 9, 7), recon="ppm", nsteps=2, rk=4)
+    print("case room", case, flush=True)
+    ref = ax.Block(w)
+    field = 8 * w.layout.npts
+    kw = {}
+    if case == "sources fail":
+        real = torch.zeros
+
+        def zeros(*a, **k):
+            if a and isinstance(a[0], tuple) and a[0] == (4,) + w.layout.shape3:
+                raise torch.OutOfMemoryError("no room")
+            return real(*a, **k)
+
+        monkeypatch.setattr(torch, "zeros", zeros)
+    elif case == "declined":
+        kw = dict(stored_geometry=False)
+    else:
+        # room for the geometry, not for a second block beside it
+        monkeypatch.setattr(torch.cuda, "mem_get_info", lambda dev=None: (100 * field, 1 << 40))
+        monkeypatch.setattr(torch.cuda, "memory_reserved", lambda dev=None: 0)
+        monkeypatch.setattr(torch.cuda, "memory_allocated", lambda dev=None: 0)
+        kw = dict(stored_geometry=True) if case == "asked for" else {}
+    blk = ax.Block(w, **kw)
+    monkeypatch.undo()
+    assert (blk.geo is not None) == (case == "asked for") and ref.geo is not None
+    assert blk.src.shape[0] == (4 if case == "asked for" else ax.SRC_FIELDS)
+    for b in (ref, blk):
+        b.run(2)
+    torch.cuda.synchronize()
+    assert torch.equal(blk.stats, ref.stats)
+    assert_fields_close(blk.state.cpu().numpy(), ref.state.cpu().numpy(), 2e-13, w.layout.owned, STATE_NAMES)
