@@ -1314,34 +1314,18 @@ DEV T recon_right_face(const T a[5], double eps, double q) {
   return wenoz_face(a[0], a[1], a[2], a[3], a[4], eps, q);
 }
 
-// Transpose of recon_right_face on its active branch (MP5, WENO-Z): ab[k] = xb d(face value) / d(a[k]).
-template <int kind>
-DEV void recon_right_face_vjp(const double a[5], double xb, double eps, double q, double ab[5]) {
+// Transpose of mp5_face on its active branch: ab[k] = xb d(face value) / d(a[k]); a side whose cotangent is zero
+// sends nothing, whatever its slopes.
+DEV void mp5_face_vjp(const double a[5], double xb, double ab[5]) {
+  Lin5 s[5];
 #pragma unroll
-  for (int k = 0; k < 5; ++k) ab[k] = 0.0;
-  if constexpr (kind == ASTERX_RECON_MP5) {
-    Lin5 s[5];
-#pragma unroll
-    for (int k = 0; k < 5; ++k) {
-      s[k] = Lin5(a[k]);
-      s[k].c[k] = 1.0;
-    }
-    const Lin5 r = mp5_face(s[0], s[1], s[2], s[3], s[4]);
-#pragma unroll
-    for (int k = 0; k < 5; ++k) ab[k] = xb != 0.0 ? xb * r.c[k] : 0.0;
-  } else {
-    // WENO-Z: one dual-number pass per stencil value.  Forward mode keeps the tangent of the
-    // Z ratio tau / (beta + eps) exact where a smoothness indicator vanishes (eps ~ 1e-40); a
-    // reverse sweep would form it as a difference of two terms of order 1 / eps.
-#pragma unroll 1
-    for (int k = 0; k < 5; ++k) {
-      Dual s[5];
-#pragma unroll
-      for (int r = 0; r < 5; ++r) s[r] = Dual(a[r], r == k ? 1.0 : 0.0);
-      const double d = recon_right_face<kind>(s, eps, q).d;
-      ab[k] = xb != 0.0 ? xb * d : 0.0;  // a side that fell back sends nothing, whatever its slopes
-    }
+  for (int k = 0; k < 5; ++k) {
+    s[k] = Lin5(a[k]);
+    s[k].c[k] = 1.0;
   }
+  const Lin5 r = mp5_face(s[0], s[1], s[2], s[3], s[4]);
+#pragma unroll
+  for (int k = 0; k < 5; ++k) ab[k] = xb != 0.0 ? xb * r.c[k] : 0.0;
 }
 
 // Both face values of a cell from its five-cell stencil: lo at its lower face (the right state there), hi at
@@ -2611,6 +2595,7 @@ struct FaceAdjArgs {
   double* gbar;
   double gam, weno_eps, weno_q;
   int speeds, riemann;
+  int rows = 0;  // points per march of the transposed reconstruction along y and z
 };
 
 template <int D, int RECON>
@@ -2789,11 +2774,26 @@ DEV void face_adj_body(const GD& g, const FaceAdjArgs& fa, unsigned tile) {
 // the exchange through LDS.  y and z: 64 columns, a march over `rows` points of each (and the two cells
 // before and after them) with the five running sums in registers.
 // Cells in [-1, n] along D have a face of [0, n]; their stencils reach [-3, n + 2], inside the ghosts.
-constexpr int RECON_ADJ_ROWS = 8;
-__host__ __device__ inline unsigned recon_adj_items(const GD& g, int D) {
+__host__ __device__ inline unsigned recon_adj_items(const GD& g, int D, int rows) {
   if (D == 0) return (unsigned)(((long long)g.ld0 * (g.n[1] + 1) * (g.n[2] + 1) + 59) / 60 * 7);
   const long long cols = (long long)(g.n[0] + 1) * (g.n[D == 1 ? 2 : 1] + 1);
-  return (unsigned)((cols + 63) / 64 * ((g.n[D] + 6 + RECON_ADJ_ROWS - 1) / RECON_ADJ_ROWS) * 7);
+  return (unsigned)((cols + 63) / 64 * ((g.n[D] + 6 + rows - 1) / rows) * 7);
+}
+// Points per march: a march of r points transposes r + 4 cells one after another, so that blocks whose marches leave
+// the chip idle take the length whose rounds of wavefronts cost least (asterx_rhs_adjoint with marches of 8, 4, 2, 1
+// points: 16^3, MP5, 225, 208, 202, 196 us; 32^3, PPM, 225, 221, 220, 225; 48^3, MP5, 380, 370, 386, 431; 64^3, PPM, 534,
+// 538, 553, 588).
+inline int recon_adj_rows(const GD& g, int D) {
+  int best = 8;
+  unsigned least = ~0u;
+  for (int r = 8; r >= 1; r /= 2) {
+    const unsigned cost = (recon_adj_items(g, D, r) + FACE_SLOTS - 1) / FACE_SLOTS * (unsigned)(r + 4);
+    if (cost < least) {
+      least = cost;
+      best = r;
+    }
+  }
+  return best;
 }
 
 // Transpose of both face values of the cell of stencil a: ab[k] goes to the point k - 2 from it.
@@ -2810,11 +2810,13 @@ DEV void recon_cell_vjp(const FaceAdjArgs& fa, const double a[5], double lb, dou
     ab[3] = hr;
   } else if constexpr (RECON == ASTERX_RECON_PPM) {
     ppm_cell_vjp(a, lb, hb, ab);
+  } else if constexpr (RECON == ASTERX_RECON_WENOZ) {
+    wenoz_cell_vjp(a, fa.weno_eps, fa.weno_q, lb, hb, ab);
   } else {
     const double b[5] = {a[4], a[3], a[2], a[1], a[0]};
     double r[5];
-    recon_right_face_vjp<RECON>(a, hb, fa.weno_eps, fa.weno_q, ab);
-    recon_right_face_vjp<RECON>(b, lb, fa.weno_eps, fa.weno_q, r);
+    mp5_face_vjp(a, hb, ab);
+    mp5_face_vjp(b, lb, r);
 #pragma unroll
     for (int k = 0; k < 5; ++k) ab[k] += r[4 - k];
   }
@@ -2857,10 +2859,10 @@ DEV void recon_adj_wave(const GD& g, const FaceAdjArgs& fa, unsigned item, doubl
     }
   } else {
     const unsigned nx = (unsigned)g.n[0] + 1, cols = nx * (unsigned)(g.n[D == 1 ? 2 : 1] + 1);
-    const unsigned nch = (unsigned)(n + 6 + RECON_ADJ_ROWS - 1) / RECON_ADJ_ROWS;
+    const unsigned nch = (unsigned)(n + 6 + fa.rows - 1) / fa.rows;
     const unsigned col = w / nch * 64 + __lane_id();
     if (col >= cols) return;
-    const int p0 = (int)(w % nch) * RECON_ADJ_ROWS - 3, p1 = min(p0 + RECON_ADJ_ROWS, n + 3);
+    const int p0 = (int)(w % nch) * fa.rows - 3, p1 = min(p0 + fa.rows, n + 3);
     const int x = (int)(col % nx) - 1, o = (int)(col / nx) - 1;
     const int base = D == 1 ? at(g, x, 0, o) : at(g, x, o, 0);
     // points inside [-3, n + 2]
@@ -4409,12 +4411,13 @@ int adj_fillT(const GD& g, double* f, int nf, hipStream_t s) {
 }
 
 template <int D, int R>
-int adj_faces_d(const GD& g, const FaceAdjArgs& fa, hipStream_t s) {
+int adj_faces_d(const GD& g, FaceAdjArgs fa, hipStream_t s) {
   int rc;
+  fa.rows = recon_adj_rows(g, D);
   const int e[3] = {g.n[0] + 1, g.n[1] + 1, g.n[2] + 1};
   if ((rc = timed(KT_ADJ, s, [&] { hipLaunchKernelGGL((k_face_adj<D, R>), dim3(face_tiles(e)), dim3(256), 0, s, g, fa); })))
     return rc;
-  return timed(KT_ADJ, s, [&] { hipLaunchKernelGGL((k_recon_adj<D, R>), dim3(recon_adj_items(g, D)), dim3(64), 0, s, g, fa); });
+  return timed(KT_ADJ, s, [&] { hipLaunchKernelGGL((k_recon_adj<D, R>), dim3(recon_adj_items(g, D, fa.rows)), dim3(64), 0, s, g, fa); });
 }
 
 template <int R>

@@ -687,6 +687,65 @@ DEV void wenoz_cell(double m2, double m1, double c0, double p1, double p2, doubl
   lo = (w0 * q0 + a1 * q1 + w2 * q2) / (6.0 * (w0 + a1 + w2));
 }
 
+// Transpose of wenoz_cell: ab[k] = hb d hi / d(a[k]) + lb d lo / d(a[k]), a[0..4] the stencil m2..p2.  The tangent of
+// each ratio r = tau / (beta + eps) is formed forward, (dtau - r dbeta) / (beta + eps), for every stencil value: exact
+// where an indicator vanishes (eps ~ 1e-40), where a reverse sweep would form it as a difference of two terms of
+// order 1 / eps.  The indicators and ratios are shared by the ten derivatives (as ten dual-number evaluations the
+// right-hand side's adjoint took 418 us at 24^3, 902 at 48^3, 1446 at 64^3; now 222, 385, 655).  A side whose cotangent is zero sends nothing, whatever its slopes.
+DEV void wenoz_cell_vjp(const double a[5], double eps, double q, double lb, double hb, double ab[5]) {
+  const double t13 = 13.0 / 12.0;
+  const double e0 = a[0] - 2.0 * a[1] + a[2], f0 = a[0] - 4.0 * a[1] + 3.0 * a[2];
+  const double e1 = a[1] - 2.0 * a[2] + a[3], f1 = a[1] - a[3];
+  const double e2 = a[2] - 2.0 * a[3] + a[4], f2 = 3.0 * a[2] - 4.0 * a[3] + a[4];
+  const double b0 = t13 * e0 * e0 + 0.25 * f0 * f0;
+  const double b1 = t13 * e1 * e1 + 0.25 * f1 * f1;
+  const double b2 = t13 * e2 * e2 + 0.25 * f2 * f2;
+  const double tau = fabs(b0 - b2);
+  const double R[3] = {1.0 / (b0 + eps), 1.0 / (b1 + eps), 1.0 / (b2 + eps)};
+  double r[3], w[3], p[3];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    r[i] = tau * R[i];
+    w[i] = 1.0 + (q != 1.0 ? pow(r[i], q) : r[i]);
+    p[i] = q != 1.0 ? q * pow(r[i], q - 1.0) : 1.0;
+  }
+  const double h0 = 2.0 * a[0] - 7.0 * a[1] + 11.0 * a[2], h1 = -a[1] + 5.0 * a[2] + 2.0 * a[3],
+               h2 = 2.0 * a[2] + 5.0 * a[3] - a[4];
+  const double l0 = 2.0 * a[2] + 5.0 * a[1] - a[0], l1 = -a[3] + 5.0 * a[2] + 2.0 * a[1],
+               l2 = 2.0 * a[4] - 7.0 * a[3] + 11.0 * a[2];
+  // weights of the three candidates at the upper (h) and the lower face (l), divided by 6 times their sum
+  const double sh = 1.0 / (6.0 * (0.1 * w[0] + 0.6 * w[1] + 0.3 * w[2]));
+  const double sl = 1.0 / (6.0 * (0.3 * w[0] + 0.6 * w[1] + 0.1 * w[2]));
+  const double H[3] = {0.1 * w[0] * sh, 0.6 * w[1] * sh, 0.3 * w[2] * sh};
+  const double Lw[3] = {0.3 * w[0] * sl, 0.6 * w[1] * sl, 0.1 * w[2] * sl};
+  // a candidate's distance from the face value, from the others' weights: exact where its own is all but one
+  const double dh01 = h0 - h1, dh02 = h0 - h2, dh12 = h1 - h2, dl01 = l0 - l1, dl02 = l0 - l2, dl12 = l1 - l2;
+  const double gh[3] = {0.6 * sh * (H[1] * dh01 + H[2] * dh02), 3.6 * sh * (H[2] * dh12 - H[0] * dh01),
+                        -1.8 * sh * (H[0] * dh02 + H[1] * dh12)};
+  const double gl[3] = {1.8 * sl * (Lw[1] * dl01 + Lw[2] * dl02), 3.6 * sl * (Lw[2] * dl12 - Lw[0] * dl01),
+                        -0.6 * sl * (Lw[0] * dl02 + Lw[1] * dl12)};
+  // the two sides' tau is one value, whose slope at zero each takes from its own difference of indicators
+  const double th = b0 - b2 < 0.0 ? -1.0 : 1.0, tl = b2 - b0 < 0.0 ? 1.0 : -1.0;
+  const double x0 = 2.0 * t13 * e0, x1 = 2.0 * t13 * e1, x2 = 2.0 * t13 * e2;
+  const double y0 = 0.5 * f0, y1 = 0.5 * f1, y2 = 0.5 * f2;
+  const double db[3][5] = {{x0 + y0, -2.0 * x0 - 4.0 * y0, x0 + 3.0 * y0, 0.0, 0.0},
+                           {0.0, x1 + y1, -2.0 * x1, x1 - y1, 0.0},
+                           {0.0, 0.0, x2 + 3.0 * y2, -2.0 * x2 - 4.0 * y2, x2 + y2}};
+  const double dh[3][5] = {{2.0, -7.0, 11.0, 0.0, 0.0}, {0.0, -1.0, 5.0, 2.0, 0.0}, {0.0, 0.0, 2.0, 5.0, -1.0}};
+#pragma unroll
+  for (int k = 0; k < 5; ++k) {
+    const double dt = db[0][k] - db[2][k];
+    double vh = 0.0, vl = 0.0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const double rh = (th * dt - r[i] * db[i][k]) * R[i], rl = (tl * dt - r[i] * db[i][k]) * R[i];
+      vh += gh[i] * (rh != 0.0 ? rh * p[i] : 0.0) + H[i] * dh[i][k];
+      vl += gl[i] * (rl != 0.0 ? rl * p[i] : 0.0) + Lw[i] * dh[2 - i][4 - k];
+    }
+    ab[k] = (hb != 0.0 ? hb * vh : 0.0) + (lb != 0.0 ? lb * vl : 0.0);
+  }
+}
+
 // A linear form sum_q c_q a_q over a 5-point stencil, with its value: the piecewise-linear
 // reconstructions evaluated on it (selections follow the value) give their gradient exactly.
 struct Lin5 {
