@@ -1558,8 +1558,10 @@ __host__ __device__ inline unsigned face_items(const int n[3], int D, int lo, in
 // upwind CT: single faces 1.112 ms, by the rule 1.058).
 template <int R>
 constexpr int face_march() { return R == ASTERX_RECON_MINMOD ? 2 : 3; }
-constexpr int FACE_BATCH_ROWS = 2;
 constexpr unsigned FACE_SLOTS = 256 * 4 * 3;  // 256 CUs of four SIMDs, three wavefronts each
+// Batches: two, or one where all patches' single faces fit the slots at once (Heun steps, MP5: four patches of 16^3 305
+// and 272 us; two of 64^3, three rounds of single faces, 1196 and 1275).
+constexpr int FACE_BATCH_ROWS = 2;
 inline int face_rows(const int n[3], int D, int lo, int march) {
   int best = 1;
   unsigned least = ~0u;
@@ -3413,7 +3415,8 @@ unsigned host_tile_blocks(const GD& g) {
   return (unsigned)(((g.n[0] + CTX - 1) / CTX) * ((g.n[1] + CTY - 1) / CTY) * ((g.n[2] + CTZ - 1) / CTZ));
 }
 
-unsigned tiles_for(int phase, const GD& g) {
+// rows: faces per march along y and z in a batch (single blocks choose their own).
+unsigned tiles_for(int phase, const GD& g, const int* rows = nullptr) {
   int e[3];
   switch (phase) {
     case PH_C2P:
@@ -3427,11 +3430,10 @@ unsigned tiles_for(int phase, const GD& g) {
       const long long cnt = G * E1 * E2 + (long long)g.n[0] * G * E2 + (long long)g.n[0] * g.n[1] * G;
       return (unsigned)((cnt + 255) / 256);
     }
-    // as in batches (single blocks choose their own march lengths)
     case PH_FACEX:
     case PH_FACEY:
     case PH_FACEZ:
-      return face_items(g.n, phase - PH_FACEX, 1, FACE_BATCH_ROWS);
+      return face_items(g.n, phase - PH_FACEX, 1, rows[phase - PH_FACEX]);
     case PH_GEOM:  // of one component
       return geom_items(g, 1, 10, geom_rows<GM_Z>());
     case PH_VERTEX:
@@ -3453,6 +3455,7 @@ struct asterx_batch {
   PatchDesc* d_patches = nullptr;
   Item* d_items[PH_N] = {};
   int nitems[PH_N] = {};
+  int rows[3] = {1, 1, 1};  // faces per march along each direction
 };
 
 namespace {
@@ -3489,7 +3492,7 @@ unsigned bgrid(const asterx_batch* b, int phase) {
 template <int D, int R>
 int face_launch(const GD& g, const asterx_batch* b, FaceArgs fa, bool uct, hipStream_t s) {
   const int lo = uct ? 3 : 1;
-  fa.rows[D] = b ? FACE_BATCH_ROWS : face_rows(g.n, D, lo, face_march<R>());
+  fa.rows[D] = b ? b->rows[D] : face_rows(g.n, D, lo, face_march<R>());
   const unsigned count = b ? 0 : face_items(g.n, D, lo, fa.rows[D]);
   if (uct) return timed(KT_FACE_X + D, s, [&] { hipLaunchKernelGGL((k_face<D, R, true>), dim3(count), dim3(64), 0, s, g, fa); });
   return RUN_WAVES(KT_FACE_X + D, PH_FACEX + D, count, (k_face<D, R, false>), (kb_face<D, R>), fa);
@@ -4259,25 +4262,31 @@ int asterx_batch_create(int32_t npatches, const asterx_grid* grids, const asterx
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) ncu = v;
   }
   b->blocks = per_cu * ncu;
+  for (int d = 1; d < 3; ++d) {
+    long long single = 0;
+    for (const GD& g : b->gds) single += face_items(g.n, d, 1, 1);
+    b->rows[d] = single <= FACE_SLOTS ? 1 : FACE_BATCH_ROWS;
+  }
+  const auto tiles = [b](int ph, int q) { return tiles_for(ph, b->gds[q], b->rows); };
   std::vector<std::vector<Item>> lists(PH_N);
   for (int ph = 0; ph < PH_N; ++ph) {
     std::vector<int> porder(npatches);
     for (int q = 0; q < npatches; ++q) porder[q] = q;
     if (order == 1)
       std::stable_sort(porder.begin(), porder.end(),
-                       [&](int x, int y) { return tiles_for(ph, b->gds[x]) > tiles_for(ph, b->gds[y]); });
+                       [&](int x, int y) { return tiles(ph, x) > tiles(ph, y); });
     std::vector<Item>& L = lists[ph];
     if (order == 2) {  // round robin over patches, largest first
       std::stable_sort(porder.begin(), porder.end(),
-                       [&](int x, int y) { return tiles_for(ph, b->gds[x]) > tiles_for(ph, b->gds[y]); });
+                       [&](int x, int y) { return tiles(ph, x) > tiles(ph, y); });
       unsigned maxt = 0;
-      for (int q = 0; q < npatches; ++q) maxt = std::max(maxt, tiles_for(ph, b->gds[q]));
+      for (int q = 0; q < npatches; ++q) maxt = std::max(maxt, tiles(ph, q));
       for (unsigned t = 0; t < maxt; ++t)
         for (int q : porder)
-          if (t < tiles_for(ph, b->gds[q])) L.push_back(Item{q, (int)t});
+          if (t < tiles(ph, q)) L.push_back(Item{q, (int)t});
     } else {
       for (int q : porder)
-        for (unsigned t = 0; t < tiles_for(ph, b->gds[q]); ++t) L.push_back(Item{q, (int)t});
+        for (unsigned t = 0; t < tiles(ph, q); ++t) L.push_back(Item{q, (int)t});
     }
     b->nitems[ph] = (int)L.size();
   }
