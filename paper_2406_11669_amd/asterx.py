@@ -548,8 +548,10 @@ class Block:
         self.k = torch.zeros_like(self.state)
         self.tmp2 = torch.zeros_like(self.state) if fused and wl.rk == 4 else None
         self.ws = torch.empty(workspace_size(self.L) // 8, dtype=torch.float64, device=dev)
+        self._small = self.L.n[0] * self.L.n[1] * self.L.n[2] <= self.ONE_STAGE_GEO_CELLS
         self._shared = 1  # stages that the current metric serves (more than one inside a step only)
         self._geo_held = False  # geo holds the current metric's data (inside a step only)
+        self._fixed = False  # nothing changes the metric within the current step
         self.red = torch.zeros(2, dtype=torch.float64, device=dev)
         self.stats = torch.zeros(6, dtype=torch.int64, device=dev)
         self.flags = torch.zeros(self.L.shape3, dtype=torch.uint8, device=dev)
@@ -567,8 +569,9 @@ class Block:
         if stored_geometry is None:
             arrays = (self.metric, self.curv, self.prim, self.state, self.tmp, self.acc, self.k, self.tmp2, self.ws)
             rest = sum(a.numel() for a in arrays if a is not None) + SRC_FIELDS * self.L.npts
-            free = torch.cuda.mem_get_info(dev)[0] + torch.cuda.memory_reserved(dev) - torch.cuda.memory_allocated(dev)
-            stored_geometry = free >= 8 * ((GEO_FIELDS + 4) * self.L.npts + rest)
+            need = 8 * ((GEO_FIELDS + 4) * self.L.npts + rest) - torch.cuda.mem_get_info(dev)[0]
+            # what torch holds and does not use counts too (asked only if needed: it takes ten times as long)
+            stored_geometry = need <= 0 or torch.cuda.memory_reserved(dev) - torch.cuda.memory_allocated(dev) >= need
         if stored_geometry:
             try:
                 self.geo = fields(torch.empty, GEO_FIELDS)
@@ -586,14 +589,10 @@ class Block:
         if self.metric_fn is not None:
             self.metric, self.curv = self.metric_fn(t)
 
-    def _metric_fixed(self):
-        """Whether no hook may change the metric within a step (also in place): neither metric_fn nor a subclass."""
-        return self.metric_fn is None and getattr(self.at_time, "__func__", None) is Block.at_time
-
     def _at_time(self, t, stages):
         """Before `stages` stages at time t."""
-        self.at_time(t)
-        if not self._metric_fixed():
+        if not self._fixed:
+            self.at_time(t)
             self._geo_held = False
             self._shared = stages
 
@@ -608,13 +607,9 @@ class Block:
         rhs(self.L, self.params, self.metric, self.curv, self.prim, U[5:8], U[8:9], self.dt, out, self.red,
             self.ws)
 
-    def _takes_geometry(self):
-        n = self.L.n
-        return self.geo is not None and (self._shared > 1 or n[0] * n[1] * n[2] <= self.ONE_STAGE_GEO_CELLS)
-
     def stage(self, U, outs):
         """c2p on U, then its right-hand side combined into outs = [(a, us, b_dt, out)]."""
-        if self.src_in_c2p and self._takes_geometry():
+        if self.src_in_c2p and self.geo is not None and (self._shared > 1 or self._small):
             if not self._geo_held:
                 geometry(self.L, self.params, self.metric, self.curv, self.geo)
                 self._geo_held = self._shared > 1
@@ -638,8 +633,10 @@ class Block:
                self.ws)
 
     def step(self):
-        # the metric is the caller's between steps: what the last one interpolated is not kept
-        self._shared, self._geo_held = self.stages_per_step if self._metric_fixed() else 1, False
+        # the metric is the caller's between steps: what the last one interpolated is not kept.  Within the step a
+        # metric_fn or a subclass's at_time may change it (also in place), else nothing does.
+        self._fixed = self.metric_fn is None and getattr(self.at_time, "__func__", None) is Block.at_time
+        self._shared, self._geo_held = self.stages_per_step if self._fixed else 1, False
         try:
             if self.fused:
                 self._step_fused()

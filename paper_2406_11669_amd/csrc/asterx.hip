@@ -2,11 +2,11 @@
 //
 // One block, one GPU.  Per RK stage the caller runs: asterx_c2p -> asterx_fill_ghosts(prim)
 // -> asterx_rhs -> asterx_rk_stage -> asterx_fill_ghosts(state).  asterx_rhs itself is
-// centre field + six launches:
-//   face<D> (D = x, y, z): reconstruction + prim->cons + fluxes + speeds + HLLE, one lane per face;
-//   cell:                  flux divergence + geometric sources + div B, LDS-tiled metric;
-//   vertex:                gauge quantities G_A and F_Psi at vertices;
-//   edge:                  FCT electric field, dA/dt and dPsi/dt.
+//   bcent, vertex: the field at the centres; gauge quantities G_A and F_Psi at vertices;
+//   faces:         reconstruction + prim->cons + fluxes + speeds + HLLE, one lane per face;
+//   cell:          flux divergence + geometric sources + div B, LDS-tiled metric;
+//   edge:          FCT electric field, dA/dt and dPsi/dt,
+// where phases that don't depend on each other share launches (do_rhs).
 // Threads map to x fastest so every stencil load is coalesced across a wavefront; the
 // block -> tile map keeps neighbouring tiles on one XCD (shared L2).  The same bodies run in
 // persistent launches over work lists of (patch, tile) items for batches of patches, and the
@@ -1466,16 +1466,14 @@ struct FaceIn {
 };
 // Without stored metric: gathered from the 16 vertices around the face, in geom_wave's order of passes (the lower
 // axis first), so that both give the same bits and blocks may choose by size.
-template <int D, int RECON>
+// NQ components are gathered together.
+template <int D, int NQ>
 DEV void face_load(const GD& g, const FaceArgs& fa, int id, FaceIn& f, bool stored = true) {
   if (fa.fma[D] && stored) {
 #pragma unroll
     for (int q = 0; q < 10; ++q) f.m[q] = ldu(q < 7 ? fa.fma[D] + (size_t)q * g.N : fa.fmb[D] + (size_t)(q - 7) * g.N, id);
   } else {
     const int s1 = D == 0 ? g.sy : 1, s2 = D == 2 ? g.sy : g.sz;
-    // two components in flight where the reconstruction leaves registers for them (asterx_rhs, 64^3: MINMOD 166 ->
-    // 162 us; PPM 168 -> 176, MP5 192 -> 201)
-    constexpr int NQ = RECON == ASTERX_RECON_MINMOD ? 2 : 1;
 #pragma unroll NQ
     for (int q = 0; q < 10; ++q) {
       const double* p = fa.metric + (size_t)q * g.N + (id - s1 - s2);
@@ -1590,7 +1588,7 @@ DEV void face_report(const FaceArgs& fa, double smax) {
 struct FaceLDS {
   FaceVals hi, lo;
 };
-template <int RECON, bool UCT>
+template <int RECON, bool UCT, int NQ>
 DEV void face_wave_x(const GD& g, const FaceArgs& fa, unsigned item, FaceLDS& L) {
   constexpr int lo = UCT ? 3 : 1;
   const unsigned e1 = g.n[1] + 2 * lo - 1, e2 = g.n[2] + 2 * lo - 1;
@@ -1601,7 +1599,7 @@ DEV void face_wave_x(const GD& g, const FaceArgs& fa, unsigned item, FaceLDS& L)
   const int id = at(g, c[0], c[1], c[2]);
   double XL[7], XR[7], smax = 0.0;
   FaceIn fin;
-  face_load<0, RECON>(g, fa, id, fin, !fa.xown || (c[1] >= 0 && c[2] >= 0));
+  face_load<0, NQ>(g, fa, id, fin, !fa.xown || (c[1] >= 0 && c[2] >= 0));
   cell_faces<0, RECON>(g, fa, id, XR, L.hi, L.lo);
   wave_lds_sync();
   if (__lane_id() > 0 && item * 63 + __lane_id() < total && c[0] >= 0) {
@@ -1613,7 +1611,7 @@ DEV void face_wave_x(const GD& g, const FaceArgs& fa, unsigned item, FaceLDS& L)
   face_report(fa, smax);
 }
 
-template <int D, int RECON, bool UCT>
+template <int D, int RECON, bool UCT, int NQ>
 DEV void face_wave_yz(const GD& g, const FaceArgs& fa, unsigned item, FaceLDS& L) {
   constexpr int lo = UCT ? 3 : 1, E = D == 1 ? 2 : 1;
   const int rows = fa.rows[D], l = __lane_id();
@@ -1641,7 +1639,7 @@ DEV void face_wave_yz(const GD& g, const FaceArgs& fa, unsigned item, FaceLDS& L
     wave_lds_sync();
     if (j >= j0 && in) {
       FaceIn fin;
-      face_load<D, RECON>(g, fa, id, fin);
+      face_load<D, NQ>(g, fa, id, fin);
       smax = fmax(smax, face_solve<D, UCT>(g, fa, id, fin, XL, XR));
     }
   }
@@ -2381,10 +2379,15 @@ __global__ __launch_bounds__(256) void kb_geom(const PatchDesc* __restrict__ P, 
 
 // 3 wavefronts per SIMD: both sides' states and fluxes of a face are live together (146-168 registers); held
 // at 4 the kernels spill (128^3, PPM: x faces 0.15 -> 0.21 ms, y 0.19 -> 0.24).
-template <int D, int R, bool UCT>
+// NQ: two components of a gathered face metric in flight where the reconstruction leaves registers for them
+// (asterx_rhs, 64^3: MINMOD 166 -> 162 us; PPM 168 -> 176, MP5 192 -> 201).  Batches, which never gather, take one:
+// their kernels are what they would be without (64 patches, MINMOD, with two: 4928 -> 4955 us per step).
+template <int R>
+constexpr int face_nq() { return R == ASTERX_RECON_MINMOD ? 2 : 1; }
+template <int D, int R, bool UCT, int NQ = face_nq<R>()>
 DEV void face_wave(const GD& g, const FaceArgs& fa, unsigned item, FaceLDS& L) {
-  if constexpr (D == 0) face_wave_x<R, UCT>(g, fa, item, L);
-  else face_wave_yz<D, R, UCT>(g, fa, item, L);
+  if constexpr (D == 0) face_wave_x<R, UCT, NQ>(g, fa, item, L);
+  else face_wave_yz<D, R, UCT, NQ>(g, fa, item, L);
 }
 template <int D, int R, bool UCT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_face(GD g, FaceArgs fa) {
@@ -2417,7 +2420,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     b.fma[D] = shifted(fa.fma[D], d.off);
     b.fmb[D] = shifted(fa.fmb[D], d.off);
     wave_lds_sync();  // the previous item's reads come before this one's writes
-    face_wave<D, R, false>(d.g, b, (unsigned)m.tile, L[threadIdx.x >> 6]);
+    face_wave<D, R, false, 1>(d.g, b, (unsigned)m.tile, L[threadIdx.x >> 6]);
   }
 }
 
