@@ -7,8 +7,8 @@ step (4 stages: c2p, primitive ghost fill, right-hand side, combine, state ghost
 captured HIP graph, with all inputs resident in HBM.
 
 Prints one JSON line: zone-updates/s per RK stage (interior cells x stages / wall time of the timed steps); the
-roofline of the dominant kernel and per-kernel figures of the face kernels, the recovery with sources and the
-divergence kernel (per-kernel HIP events recorded live on the launch stream); the whole-stage HBM and FP64
+roofline of the dominant kernel and per-kernel figures of the faces, the recovery with sources and the divergence
+with the edges (per-kernel HIP events recorded live on the launch stream); the whole-stage HBM and FP64
 rooflines; the same block with the other reconstruction, batched patches against a per-patch loop, the learned
 recovery guess against the plain one, one adjoint gradient, forward and reverse, and the paper's own single-GPU
 benchmark (its Setup A, a magnetized TOV star at 240^3) in the paper's zone-cycles/s beside the paper's figure
@@ -33,25 +33,32 @@ FP64_VECTOR_PEAK_TFLOPS = 78.6   # MI355X FP64 vector (256 CUs x 128 FLOP/clk x 
 # with the metric interpolation) and about 6.4 kFLOP per zone-stage in all; 514 B per zone-stage of RK4.
 SURVEY_FLOPS_PER_FACE = 1400.0
 SURVEY_FLOPS_PER_ZONE_STAGE = 6400.0
-# Algorithmic FP64 operations per face of the face kernel (reconstruction of 7 variables on both sides,
-# 16-point face metric of 10 components, prim->cons, fluxes, quartic speeds, HLLE or LxF), counted by running
-# the plain serial implementation on an operation-counting scalar (+, -, *, /, sqrt, pow = 1 each) over the
-# 3 x 129^3 faces of the 128^3 block of this workload (same seed and recipe; limiter branches make the count
-# data dependent).
-FACE_FLOPS = {"ppm": 2603.1, "wenoz": 3955.0, "minmod": 2022.6, "mp5": 2480.3, "ppm+lxf": 2581.1,
-              "ppm+hlle+uct": 2620.8}
+# Algorithmic FP64 operations per face (reconstruction of 7 variables on both sides, 16-point face metric of 10
+# components, prim->cons, fluxes, quartic speeds, HLLE or LxF), counted by running the plain serial implementation on
+# an operation-counting scalar (+, -, *, /, sqrt, pow = 1 each) over the 3 x 129^3 faces of the 128^3 block of this
+# workload (same seed and recipe; limiter branches make the count data dependent).  The face metric's interpolation,
+# 5 four-point passes of 7 operations for each of 10 components, is not the face kernel's here (it reads stored data).
+FACE_INTERP_FLOPS = 10 * 35.0
+FACE_FLOPS = {k: v - FACE_INTERP_FLOPS for k, v in
+              {"ppm": 2603.1, "wenoz": 3955.0, "minmod": 2022.6, "mp5": 2480.3, "ppm+lxf": 2581.1,
+               "ppm+hlle+uct": 2620.8}.items()}
 # The same count per owned cell of the cell kernel (centre metric values and derivatives, curvature values,
 # sources, flux divergence) and of the recovery (centre metric values, centre field, geometry, warm-started
 # Noble iteration) on that block.
 CELL_FLOPS = 4716.0
 C2P_FLOPS = 1795.0
+# Of these, the interpolation to the centre: the ten components' values and derivatives (294 operations each) and the
+# six curvature values (147 each) in the cell kernel, ten values in the recovery.
+CENTRE_INTERP_FLOPS = 10 * 294.0 + 6 * 147.0
+C2P_INTERP_FLOPS = 10 * 147.0
 # The benchmark's stage evaluates the sources in the recovery kernel, from spacetime data interpolated once per step
 # (asterx_geometry, asterx_c2p_geo), and leaves the flux divergence, div B and the stage outputs to a streaming
 # kernel (asterx_rhs_rk_geo).  Counted per cell: the divergence 5 components x (3 differences, 3 divisions by the
 # spacing, 3 additions, 1 source addition) = 50, and div B 6 face curls x 5 (the counter's face_B) + 3 differences +
-# 3 divisions + 2 additions = 38.  The counts above contain the interpolation, which the stored data leaves out of
-# the stages (10 values per face; per cell 10 values, 30 derivatives, 6 curvature values): no count for the recovery.
+# 3 divisions + 2 additions = 38.  The recovery with sources: what the recovery and the cell kernel do beside the
+# interpolation and the divergence.
 DIV_FLOPS = 50.0 + 38.0
+C2P_GEO_FLOPS = C2P_FLOPS - C2P_INTERP_FLOPS + CELL_FLOPS - CENTRE_INTERP_FLOPS - DIV_FLOPS
 # The edge kernel shares the divergence's launch.  Counted per cell (flux CT, Lorenz gauge): three edge averages of
 # four fluxes 12, three gradients of the gauge quantity 9, its divergence 8, the damping term 3.
 EDGE_FLOPS = 32.0
@@ -81,9 +88,20 @@ STAGE_BYTES_RK4 = 514.0
 # Whole-stage algorithmic FP64 operations per zone-stage at 128^3 (same counting scalar, over one
 # right-hand side and one c2p of the 128^3 block of this workload; for PPM: centre field 41, faces of
 # the three directions 7994, cell sources and divergence 4716, constrained transport and gauge 139, c2p
-# 1795; the RK combine's 2 operations per field are not counted).
+# 1795; the RK combine's 2 operations per field are not counted).  stage_flops() charges the interpolation of the
+# spacetime data once per step, as the benchmark's stages do it.
 STAGE_FLOPS = {"ppm": 14684.9, "wenoz": 18836.6, "minmod": 12902.4, "mp5": 14307.9, "ppm+lxf": 14617.3,
                "ppm+hlle+uct": 16669.8}  # upwind CT: 129 x 133^2 faces per direction, edge field 1561
+
+
+def stage_flops(scheme, ct, stages):
+    if scheme not in STAGE_FLOPS:
+        return None
+    faces = 3 * 129.0 * (129.0 ** 2 if ct == "fct" else 133.0 ** 2) / 128.0 ** 3
+    once = faces * FACE_INTERP_FLOPS + CENTRE_INTERP_FLOPS
+    return round(STAGE_FLOPS[scheme] - once - C2P_INTERP_FLOPS + once / stages, 1)
+
+
 RIDGE = FP64_VECTOR_PEAK_TFLOPS * 1e3 / HBM_PEAK_GBS   # FLOP/B where the FP64 and HBM roofs meet
 
 
@@ -322,8 +340,8 @@ def kernel_rooflines(kt, stages, n, scheme, ct):
         "faces": dict(ms=avg("faces"), launches_per_stage=1, units="faces", units_per_launch=3 * faces,
                       flops={"estimate": SURVEY_FLOPS_PER_FACE, "oracle_count": FACE_FLOPS.get(scheme)},
                       bytes=FACE_BYTES),
-        "c2p_geo": dict(ms=avg("c2p"), launches_per_stage=1, units="cells", units_per_launch=cells, flops={},
-                        bytes=C2P_GEO_BYTES),
+        "c2p_geo": dict(ms=avg("c2p"), launches_per_stage=1, units="cells", units_per_launch=cells,
+                        flops={"oracle_count": C2P_GEO_FLOPS}, bytes=C2P_GEO_BYTES),
         "divergence+edge": dict(ms=avg("divergence+edge"), launches_per_stage=1, units="cells",
                                 units_per_launch=cells,
                                 flops={"oracle_count": DIV_FLOPS + EDGE_FLOPS} if ct == "fct" else {},
@@ -574,9 +592,9 @@ def main():
     stage_gbs = STAGE_BYTES_RK4 * value / 1e9
     hbm = {"bytes_per_zone_stage": STAGE_BYTES_RK4, "achieved": round(stage_gbs, 1), "peak": HBM_PEAK_GBS,
            "unit": "GB/s", "frac": round(stage_gbs / HBM_PEAK_GBS, 4)}
-    stage_flops = STAGE_FLOPS.get(scheme) if n == 128 else None
+    counted = stage_flops(scheme, args.ct, stages) if n == 128 else None
     fp64 = {"unit": "TFLOP/s", "peak": FP64_VECTOR_PEAK_TFLOPS}
-    for src, f in (("estimate", SURVEY_FLOPS_PER_ZONE_STAGE), ("oracle_count", stage_flops)):
+    for src, f in (("estimate", SURVEY_FLOPS_PER_ZONE_STAGE), ("oracle_count", counted)):
         if f:
             fp64["flops_per_zone_stage_" + src] = f
             fp64["frac_" + src] = round(f * value / 1e12 / FP64_VECTOR_PEAK_TFLOPS, 4)

@@ -367,8 +367,9 @@ int asterx_c2p_learned(const asterx_grid* g, const asterx_params* p, const doubl
  * extrinsic curvature.  asterx_c2p_src recovers the primitives (asterx_c2p, or asterx_c2p_learned
  * when mlp is not NULL) and then evaluates these sources from the recovered state in the same
  * kernel, whose centre-metric values serve both; asterx_rhs_rk_src is asterx_rhs_rk with the
- * sources taken from there.  The pair gives bitwise the results of asterx_c2p (or
- * asterx_c2p_learned) followed by asterx_rhs_rk.
+ * sources taken from there.  The pair gives the results of asterx_c2p (or asterx_c2p_learned)
+ * followed by asterx_rhs_rk up to rounding, 1e-13 of the fields' scales (the interpolation passes
+ * run in another order).
  * c2p_src: curv is K_ij at vertices ([6], as in asterx_rhs); src (device, ASTERX_SRC_FIELDS
  * fields of the block's index space, out): fields 0-3 receive alpha sqrt(gamma) times the sources
  * of S_x, S_y, S_z and tau on owned cells (that of D is 0); fields 4-13 the ten metric components
